@@ -235,10 +235,10 @@ __device__ __forceinline__ void k_write_stage(const uint32_t* w, uint8_t* __rest
     }
 }
 
-// Operand fragment of token st (0..3 of the lane's four) from one K-step's directly loaded fields.
+// Fields of token st (0..3 of the lane's four) from one K-step's directly loaded words. A 1-bit plane's
+// field is the upper half of its word for odd st (two tokens share a word).
 template <int B>
-__device__ __forceinline__ v4i k_frag_direct(const uint32_t* w, int st) {
-    Fld f[3];
+__device__ __forceinline__ void k_fields_direct(const uint32_t* w, int st, Fld (&f)[3]) {
     int o = 0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -253,14 +253,20 @@ __device__ __forceinline__ v4i k_frag_direct(const uint32_t* w, int st) {
             f[k] = Fld{0u, 0u, 0u, 0u};
         }
     }
+}
+
+// Operand fragment of token st from one K-step's directly loaded fields.
+template <int B>
+__device__ __forceinline__ v4i k_frag_direct(const uint32_t* w, int st) {
+    Fld f[3];
+    k_fields_direct<B>(w, st, f);
     return unpack16<B>(f, (st & 1) != 0);
 }
 
-// Operand fragment of a token from the staged K-step: its field of plane k starts at bit p * x of the
-// plane's staged region.
+// Fields of a token from the staged K-step: its field of plane k starts at bit p * x of the plane's
+// staged region.
 template <int B>
-__device__ __forceinline__ v4i k_frag_staged(const uint8_t* __restrict__ stage, uint32_t x) {
-    Fld f[3];
+__device__ __forceinline__ void k_fields_staged(const uint8_t* __restrict__ stage, uint32_t x, Fld (&f)[3]) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         if (k < n_planes(B)) {
@@ -281,6 +287,13 @@ __device__ __forceinline__ v4i k_frag_staged(const uint8_t* __restrict__ stage, 
             f[k] = Fld{0u, 0u, 0u, 0u};
         }
     }
+}
+
+// Operand fragment of a token from the staged K-step.
+template <int B>
+__device__ __forceinline__ v4i k_frag_staged(const uint8_t* __restrict__ stage, uint32_t x) {
+    Fld f[3];
+    k_fields_staged<B>(stage, x, f);
     return unpack16<B>(f, false);
 }
 

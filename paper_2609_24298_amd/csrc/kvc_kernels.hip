@@ -1,6 +1,6 @@
 // Device half of libkvc, compression side: HIP kernels for CDNA4 (gfx950) and
-// their C-ABI launchers (kvc_encode, kvc_reconstruct). Decode attention lives
-// in kvc_decode.hip.
+// their C-ABI launchers (kvc_encode, kvc_encode_kv). Decode attention lives in
+// kvc_decode.hip, reconstruction in kvc_recon.hip.
 //
 // Kernels
 //  encode_mfma_kernel   bulk encode: per (unit, run of 64-token tiles), the
@@ -12,7 +12,6 @@
 //                       rows read coalesced, the same bounded decision (undecided
 //                       elements settled by their wavefront), and the new fields
 //                       written in place (whole words where a token owns them).
-//  reconstruct_kernel   x_hat = P^T z for a 64-token block of one unit.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -486,63 +485,8 @@ __global__ __launch_bounds__(kAppThreads) void append_kv_kernel(DevSide k, DevSi
     else append_unit(v, KVC_SIDE_V, xv, xv_stride, t0, n_tok, blockIdx.x);
 }
 
-// ---------------------------------------------------------------- reconstruct
-
-constexpr int kRecThreads = 256;
-
-__global__ __launch_bounds__(kRecThreads) void reconstruct_kernel(DevSide s, int side, int t0, int n_tok, float* __restrict__ out) {
-    extern __shared__ float smem[];
-    const int u = blockIdx.y;
-    const int blk0 = t0 + blockIdx.x * kTile;  // first token of this block
-    const int r = s.r[u], b = s.b[u];
-    const float step = s.delta[u];
-    const float half = (float)(1 << (b - 1)) - 0.5f;
-    const uint16_t* __restrict__ P = s.basis + s.basis_off[u];
-    const uint8_t* __restrict__ stream = s.codes + s.code_off[u];
-    float* Ps = smem;            // [r][128]
-    float* zh = Ps + r * kD;     // [64][r + 1]
-    const int zs = r + 1;
-    for (int k = threadIdx.x; k < r * kD; k += kRecThreads) Ps[k] = h2f((P[k]));
-    for (int k = threadIdx.x; k < kTile * r; k += kRecThreads) {
-        const int tt = k / r, i = k - tt * r;
-        const int tok = blk0 + tt;
-        float z = 0.f;
-        if (tok < t0 + n_tok) {
-            const uint8_t* tile = stream + (int64_t)(tok / kTile) * 8 * r * b;
-            const int tl = tok % kTile;
-            const uint32_t code = side == KVC_SIDE_K ? load_code(tile, r, b, slot_k(tl, i, r)) : load_code_v(tile, r, b, tl, i);
-            z = ((float)code - half) * step;
-        }
-        zh[tt * zs + i] = z;
-    }
-    __syncthreads();
-    const int j = threadIdx.x & (kD - 1);
-    for (int tt = threadIdx.x >> 7; tt < kTile; tt += kRecThreads / kD) {
-        const int tok = blk0 + tt;
-        if (tok >= t0 + n_tok) break;
-        float o = 0.f;
-        for (int i = 0; i < r; ++i) o = fmaf(Ps[i * kD + j], zh[tt * zs + i], o);
-        out[((int64_t)u * n_tok + (tok - t0)) * kD + j] = o;
-    }
-}
-
 // ---------------------------------------------------------------- host side
 
-namespace {
-
-int max_r(const kvc_stream_desc* s) {
-    int m = 2;
-    for (int u = 0; u < s->n_units; ++u) m = s->r_host[u] > m ? s->r_host[u] : m;
-    return m;
-}
-
-int set_smem_limit(const void* fn, size_t bytes) {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e != hipSuccess) return set_error(KVC_EDEVICE, "hipFuncSetAttribute: %s", hipGetErrorString(e));
-    return KVC_OK;
-}
-
-}  // namespace
 }  // namespace kvc
 
 using namespace kvc;
@@ -597,20 +541,4 @@ extern "C" int kvc_encode_kv(const kvc_stream_desc* k, const kvc_stream_desc* v,
     hipLaunchKernelGGL(append_kv_kernel, dim3(k->n_units, 2), dim3(kAppThreads), 0, (hipStream_t)stream, dev_side(k),
                        dev_side(v), xk, xk_unit_stride, xv, xv_unit_stride, t0, n_tok);
     return check_launch("kvc_encode_kv");
-}
-
-extern "C" int kvc_reconstruct(const kvc_stream_desc* s, int32_t t0, int32_t n_tok, float* out, void* stream) {
-    clear_error();
-    if (int e = validate_desc(s, "kvc_reconstruct")) return e;
-    if (t0 < 0 || n_tok < 0) return set_error(KVC_EINVAL, "kvc_reconstruct: negative t0 or n_tok");
-    if ((int64_t)t0 + n_tok > s->capacity) return set_error(KVC_ENOSPACE, "kvc_reconstruct: t0 + n_tok > capacity");
-    if (n_tok == 0 || s->n_units == 0) return KVC_OK;
-    if (!out) return set_error(KVC_EINVAL, "kvc_reconstruct: null output");
-    const int r = max_r(s);
-    const size_t smem = (size_t)r * kD * 4 + (size_t)kTile * (r + 1) * 4;
-    if (int e = set_smem_limit((const void*)reconstruct_kernel, smem)) return e;
-    dim3 grid((n_tok + kTile - 1) / kTile, s->n_units);
-    hipLaunchKernelGGL(reconstruct_kernel, grid, dim3(kRecThreads), smem, (hipStream_t)stream, dev_side(s), s->side, t0,
-                       n_tok, out);
-    return check_launch("kvc_reconstruct");
 }
