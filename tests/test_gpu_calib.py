@@ -141,3 +141,22 @@ def test_device_calibration_tables_match_oracle(covs8b):
     log(f"[calibration chain] identical (r, b) on {same:.1%} of {len(covs)} heads; total D {ta:.6e} vs {tb:.6e}")
     assert same >= 0.9
     assert abs(ta - tb) <= 1e-3 * tb
+
+
+@pytest.mark.parametrize("H,n_tok,centered", [(1, 1, True), (9, 63, True), (17, 64, False), (3, 513, True), (8, 1100, False)])
+def test_covariance_chunk_edges(H, n_tok, centered):
+    # heads not a multiple of eight, tokens around the 64-token chunks and the 512 of one turn of the wavefronts;
+    # fp32 sums of n_tok exact products (n_tok 2^-24 of the sum of magnitudes) and the mean's rounding
+    rng = np.random.default_rng(H * 1000 + n_tok)
+    x = (rng.standard_normal((H, n_tok + 2, 128)) + 0.25 * rng.standard_normal((H, 1, 128))).astype(np.float16)
+    cov = torch.full((H, 128, 128), np.nan, dtype=torch.float32, device="cuda")
+    kvc.kvc_covariance(torch.as_tensor(x.view(np.int16), device="cuda").view(torch.float16), n_tok, cov, centered)
+    torch.cuda.synchronize()
+    got = cov.cpu().numpy().astype(np.float64)
+    for h in range(H):
+        X = x[h, :n_tok].astype(np.float64)
+        ref, mag = X.T @ X / n_tok, np.abs(X).T @ np.abs(X) / n_tok
+        if centered:
+            ref, mag = ref - np.outer(X.mean(0), X.mean(0)), mag + np.outer(np.abs(X).mean(0), np.abs(X).mean(0))
+        assert np.all(np.abs(got[h] - ref) <= (n_tok + 8) * 2.0 ** -24 * mag), h
+        assert np.array_equal(got[h], got[h].T), h
