@@ -89,11 +89,12 @@ __device__ __forceinline__ double wave_sum(double v) {
 // enough from every threshold for the code to be certain. jn is a threshold index near y / step;
 // the sign of y - jn step is certain when |y - jn step| exceeds the bound, and then (for
 // e < step / 4) y lies between the jn - 1 and jn + 1 thresholds.
-__device__ __forceinline__ bool certain_code(double y, float step, int b, float pn, float xn, uint32_t& code) {
+// inv = 1 / step in fp64.
+__device__ __forceinline__ bool certain_code(double y, float step, double inv, int b, float pn, float xn, uint32_t& code) {
     const double e = 0x1p-45 * (double)pn * (double)xn * 1.01;
     const int h = 1 << (b - 1);
     const double st = step;
-    const double jn = rint(y * (1.0 / st));
+    const double jn = rint(y * inv);
     const double d = fma(-jn, st, y);
     if (e < 0.25 * st && fabs(d) > e + 0x1p-50 * fabs(y) && fabs(d) < 0.75 * st) {
         code = (uint32_t)fmin(fmax(jn - (d < 0.0 ? 1.0 : 0.0) + h, 0.0), (double)((1 << b) - 1));
@@ -103,18 +104,17 @@ __device__ __forceinline__ bool certain_code(double y, float step, int b, float 
 }
 
 // Code of coordinate c for token row `xrow`, decided by the whole wavefront: fp64 sum of the 128
-// exact products (lane takes j = 2 lane, 2 lane + 1), then the exact path if still undecided.
-// Uniform across the wavefront.
-__device__ uint32_t resolve_code_wave(const uint16_t* __restrict__ Pl_row, const uint16_t* __restrict__ Pg_row,
-                                      const uint16_t* __restrict__ xrow, float step, int b, float pn, float xn,
+// exact products (lane takes j = 2 lane, 2 lane + 1: the pair xw of the token's row), then the exact
+// path if still undecided. Uniform across the wavefront. inv = 1 / step in fp64.
+__device__ uint32_t resolve_code_wave(const uint16_t* __restrict__ Pl_row, const uint16_t* __restrict__ Pg_row, uint32_t xw,
+                                      const uint16_t* __restrict__ xrow, float step, double inv, int b, float pn, float xn,
                                       int lane) {
     const uint32_t pw = *reinterpret_cast<const uint32_t*>(Pl_row + 2 * lane);
-    const uint32_t xw = *reinterpret_cast<const uint32_t*>(xrow + 2 * lane);
     const double s = (double)h2f((uint16_t)(pw & 0xffff)) * (double)h2f((uint16_t)(xw & 0xffff)) +
                      (double)h2f((uint16_t)(pw >> 16)) * (double)h2f((uint16_t)(xw >> 16));
     const double y = wave_sum(s);
     uint32_t code;
-    if (certain_code(y, step, b, pn, xn, code)) return code;
+    if (certain_code(y, step, inv, b, pn, xn, code)) return code;
     return exact_code(Pg_row, xrow, step, b);
 }
 
@@ -210,7 +210,9 @@ __device__ __forceinline__ void append_unit(const DevSide& s, int side, const ui
                 m &= m - 1;
                 const int il = (i & ~63) + l;
                 const uint16_t* Prow = P + (int64_t)il * KVC_HEAD_DIM;
-                const uint32_t cl = resolve_code_wave(Prow, Prow, xu + (int64_t)t * KVC_HEAD_DIM, step, b, sqrtf(pns[il]), xn, lane);
+                const uint16_t* xrow = xu + (int64_t)t * KVC_HEAD_DIM;
+                const uint32_t cl = resolve_code_wave(Prow, Prow, *reinterpret_cast<const uint32_t*>(xrow + 2 * lane), xrow, step,
+                                                      1.0 / (double)step, b, sqrtf(pns[il]), xn, lane);
                 if (lane == l) code = cl;
             }
             if (i < r) cs[t][i] = (uint8_t)code;

@@ -1767,17 +1767,6 @@ int resident_blocks(size_t smem) {
     return nb;
 }
 
-// Compute units of the current device (256, the MI355X figure, without a device).
-int device_cus() {
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        ncu <= 0) {
-        (void)hipGetLastError();
-        ncu = 256;
-    }
-    return ncu;
-}
-
 // Work items (wavefronts) the device holds at once for this launch.
 int64_t resident_slots(int G, size_t smem) {
     const int ncu = device_cus();

@@ -152,6 +152,17 @@ inline DevSide dev_side(const kvc_stream_desc* s) {
     return DevSide{s->r, s->b, s->code_off, s->basis_off, s->delta, s->codes, s->basis};
 }
 
+// Compute units of the current device (256, the MI355X figure, without a device).
+inline int device_cus() {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        ncu <= 0) {
+        (void)hipGetLastError();
+        ncu = 256;
+    }
+    return ncu;
+}
+
 inline int check_launch(const char* what) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(KVC_EDEVICE, "%s: %s", what, hipGetErrorString(e));
