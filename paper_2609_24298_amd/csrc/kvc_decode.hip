@@ -745,6 +745,105 @@ __device__ __forceinline__ const uint8_t* uni(const uint8_t* p) {
     return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
 }
 
+// Raise of the running maxima (rare): each head whose tile beats its max by more than 2^kLazy (every head
+// on the first tile) takes the tile's own max, and its accumulators are rescaled (every limb of a (head,
+// coordinate) sits in this lane): value = C0 + 2^8 C1 + 2^16 C2 + 2^24 C3 (exact in fp64: |value| <= 2^53)
+// -> rint(value alpha), split again into C3 and three bytes. s holds the logits less the old max (the raw
+// logits on the first tile), ml the lane's own maxima; mb = bias - max afterwards.
+template <int LM>
+__device__ __forceinline__ void raise_max(bool first, const float (&ml)[LM], const float (&bias)[LM], float (&s)[LM][4],
+                                          float (&mrun)[LM], float (&mb)[LM], v4i (&C)[LM][9]) {
+    float mx[LM];
+#pragma unroll
+    for (int lm = 0; lm < LM; ++lm) mx[lm] = row_max(ml[lm]);
+#pragma unroll
+    for (int lm = 0; lm < LM; ++lm) {
+        if ((first && mx[lm] > -INFINITY) || mx[lm] > kLazy) {
+            const float mold = mrun[lm];
+            const float shift = first ? 0.f : mold;  // s + shift = the raw logit
+            const float mnew = mx[lm] + shift;
+            const float alpha = first ? 0.f : exp2f(mold - mnew);
+            mrun[lm] = mnew;
+            mb[lm] = bias[lm] - mnew;
+#pragma unroll
+            for (int st = 0; st < 4; ++st) s[lm][st] = (s[lm][st] + shift) - mnew;
+            if (!first) {
+                const double a = (double)alpha;
+#pragma unroll
+                for (int nt = 0; nt < 9; ++nt) {
+                    const double v = ((double)C[lm][nt][0] + 256.0 * (double)C[lm][nt][1]) +
+                                     (65536.0 * (double)C[lm][nt][2] + 16777216.0 * (double)C[lm][nt][3]);
+                    const double vs = rint(v * a);
+                    const double c3 = floor(vs * (1.0 / 16777216.0));
+                    const double r3 = vs - 16777216.0 * c3;  // [0, 2^24): exact from here on
+                    const double c2 = floor(r3 * (1.0 / 65536.0));
+                    const double r2 = r3 - 65536.0 * c2;
+                    const double c1 = floor(r2 * (1.0 / 256.0));
+                    C[lm][nt][3] = (int)c3;
+                    C[lm][nt][2] = (int)c2;
+                    C[lm][nt][1] = (int)c1;
+                    C[lm][nt][0] = (int)(r2 - 256.0 * c1);
+                }
+            }
+        }
+    }
+}
+
+// Probability limbs of the lane's four tokens: P'' = round(p kPScale) + 0x808080; bytes 0, 1, 2 (xor 0x80)
+// and 3 are the limbs S0..S3 with P = S0 + 2^8 S1 + 2^16 S2 + 2^24 S3. LDS row 4 h + limb, bytes 4 col + st.
+// Every lane writes (heads past G have -inf logits, so zero limbs): no divergent LDS writes.
+template <int LM>
+__device__ __forceinline__ void write_limbs(const float (&s)[LM][4], uint8_t* __restrict__ pmat, int col, int grp) {
+#pragma unroll
+    for (int lm = 0; lm < LM; ++lm) {
+        uint32_t P[4];
+#pragma unroll
+        for (int st = 0; st < 4; ++st) P[st] = (uint32_t)fmaf(__builtin_amdgcn_exp2f(s[lm][st]), kPScale, kPBias);
+        const uint32_t q01 = perm(P[1], P[0], 0x05010400u), q23 = perm(P[3], P[2], 0x05010400u);
+        const uint32_t r01 = perm(P[1], P[0], 0x07030602u), r23 = perm(P[3], P[2], 0x07030602u);
+        const uint32_t L0 = perm(q23, q01, 0x05040100u) ^ 0x80808080u;
+        const uint32_t L1 = perm(q23, q01, 0x07060302u) ^ 0x80808080u;
+        const uint32_t L2 = perm(r23, r01, 0x05040100u) ^ 0x80808080u;
+        const uint32_t L3 = perm(r23, r01, 0x07060302u);
+        uint8_t* row = pmat + (16 * lm + 4 * grp) * kPRowBytes + 4 * col;
+        *reinterpret_cast<uint32_t*>(row) = L0;
+        *reinterpret_cast<uint32_t*>(row + kPRowBytes) = L1;
+        *reinterpret_cast<uint32_t*>(row + 2 * kPRowBytes) = L2;
+        *reinterpret_cast<uint32_t*>(row + 3 * kPRowBytes) = L3;
+    }
+}
+
+// Partial of each head: m, l = sum of P (all-ones column), centred accumulator. Lane (grp, col)
+// holds every limb of head 4 pm + grp at coordinate 16 nt + col; the all-ones column is col 0.
+template <int G>
+__device__ __forceinline__ void write_partial(const v4i (&C)[Shape<G>::LM][9], const float (&mrun)[Shape<G>::LM], int rv, int hv,
+                                              float* __restrict__ out, int lane) {
+    const int col = lane & 15, grp = lane >> 4, nv = (rv + 15) >> 4;
+#pragma unroll
+    for (int pm = 0; pm < Shape<G>::LM; ++pm) {
+        const int h = 4 * pm + grp;
+        const int o0 = __shfl(C[pm][8][0], lane & 48), o1 = __shfl(C[pm][8][1], lane & 48),
+                  o2 = __shfl(C[pm][8][2], lane & 48), o3 = __shfl(C[pm][8][3], lane & 48);
+        if (G % 4 == 0 || h < G) {
+            float* o = out + h * kPartStride;
+            if (col == 0) {
+                o[0] = mrun[pm];
+                o[1] = ((float)o0 + 256.f * (float)o1) + (65536.f * (float)o2 + 16777216.f * (float)o3);
+            }
+#pragma unroll
+            for (int nt = 0; nt < 8; ++nt) {
+                const int cc = 16 * nt + col;
+                if (nt < nv) {
+                    const int a0 = C[pm][nt][0] - hv * o0, a1 = C[pm][nt][1] - hv * o1, a2 = C[pm][nt][2] - hv * o2,
+                              a3 = C[pm][nt][3] - hv * o3;
+                    o[4 + cc] = cc < rv ? ((float)a0 + 256.f * (float)a1) + (65536.f * (float)a2 + 16777216.f * (float)a3)
+                                        : 0.f;
+                }
+            }
+        }
+    }
+}
+
 // Inlined into the kernel: each instantiation is a disjoint branch of the dispatch, so registers
 // are allocated per branch, and no call frame saves registers to scratch memory on every item.
 template <int G, int BKc, int BVc, int KM, int NVc>
@@ -763,7 +862,7 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
     v_cap_tiles = uni(v_cap_tiles);
     const int rk = uni(K.r[u]), bk = uni(K.b[u]), rv = uni(V.r[u]), bv = uni(V.b[u]);
     const int hv = bv == 8 ? 0 : (1 << (bv - 1));
-    const int nk = (rk + 63) >> 6, nv = (rv + 15) >> 4;
+    const int nk = (rk + 63) >> 6;
     const int g16 = rk >> 4, rho = rk & 15;
     const int ks_t = rho ? (g16 >> 2) : 2;  // K-step holding the tail group (2: none)
     const int ktb = 8 * rk * bk, vtb = 8 * rv * bv;
@@ -898,68 +997,9 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
             ml[lm] = fmaxf(fmaxf(s[lm][0], s[lm][1]), fmaxf(s[lm][2], s[lm][3]));
             raise = raise || ml[lm] > kLazy;
         }
-        if (__any(raise)) {
-            float mx[LM];
-#pragma unroll
-            for (int lm = 0; lm < LM; ++lm) mx[lm] = row_max(ml[lm]);
-            // Raise the max of each head whose tile beats it by more than 2^kLazy (every head on the
-            // first tile) to the tile's own max, and rescale that head's accumulators (every limb of a
-            // (head, coordinate) sits in this lane): value = C0 + 2^8 C1 + 2^16 C2 + 2^24 C3 (exact in
-            // fp64: |value| <= 2^53) -> rint(value alpha), split again into C3 and three bytes.
-#pragma unroll
-            for (int lm = 0; lm < LM; ++lm) {
-                if ((first && mx[lm] > -INFINITY) || mx[lm] > kLazy) {
-                    const float mold = mrun[lm];
-                    const float shift = first ? 0.f : mold;  // s + shift = the raw logit
-                    const float mnew = mx[lm] + shift;
-                    const float alpha = first ? 0.f : exp2f(mold - mnew);
-                    mrun[lm] = mnew;
-                    mb[lm] = bias[lm] - mnew;
-#pragma unroll
-                    for (int st = 0; st < 4; ++st) s[lm][st] = (s[lm][st] + shift) - mnew;
-                    if (!first) {
-                        const double a = (double)alpha;
-#pragma unroll
-                        for (int nt = 0; nt < 9; ++nt) {
-                            const double v = ((double)C[lm][nt][0] + 256.0 * (double)C[lm][nt][1]) +
-                                             (65536.0 * (double)C[lm][nt][2] + 16777216.0 * (double)C[lm][nt][3]);
-                            const double vs = rint(v * a);
-                            const double c3 = floor(vs * (1.0 / 16777216.0));
-                            const double r3 = vs - 16777216.0 * c3;  // [0, 2^24): exact from here on
-                            const double c2 = floor(r3 * (1.0 / 65536.0));
-                            const double r2 = r3 - 65536.0 * c2;
-                            const double c1 = floor(r2 * (1.0 / 256.0));
-                            C[lm][nt][3] = (int)c3;
-                            C[lm][nt][2] = (int)c2;
-                            C[lm][nt][1] = (int)c1;
-                            C[lm][nt][0] = (int)(r2 - 256.0 * c1);
-                        }
-                    }
-                }
-            }
-        }
+        if (__any(raise)) raise_max<LM>(first, ml, bias, s, mrun, mb, C);
 
-        // ---- probability limbs: P'' = round(p kPScale) + 0x808080; bytes 0, 1, 2 (xor 0x80) and 3 are
-        // the limbs S0..S3 with P = S0 + 2^8 S1 + 2^16 S2 + 2^24 S3. Row 4 h + limb, bytes 4 col + st.
-#pragma unroll
-        for (int lm = 0; lm < LM; ++lm) {
-            uint32_t P[4];
-#pragma unroll
-            for (int st = 0; st < 4; ++st)
-                P[st] = (uint32_t)fmaf(__builtin_amdgcn_exp2f(s[lm][st]), kPScale, kPBias);
-            const uint32_t q01 = perm(P[1], P[0], 0x05010400u), q23 = perm(P[3], P[2], 0x05010400u);
-            const uint32_t r01 = perm(P[1], P[0], 0x07030602u), r23 = perm(P[3], P[2], 0x07030602u);
-            const uint32_t L0 = perm(q23, q01, 0x05040100u) ^ 0x80808080u;
-            const uint32_t L1 = perm(q23, q01, 0x07060302u) ^ 0x80808080u;
-            const uint32_t L2 = perm(r23, r01, 0x05040100u) ^ 0x80808080u;
-            const uint32_t L3 = perm(r23, r01, 0x07060302u);
-            // every lane writes (heads past G have -inf logits, so zero limbs): no divergent LDS writes
-            uint8_t* row = pmat + (16 * lm + 4 * grp) * kPRowBytes + 4 * col;
-            *reinterpret_cast<uint32_t*>(row) = L0;
-            *reinterpret_cast<uint32_t*>(row + kPRowBytes) = L1;
-            *reinterpret_cast<uint32_t*>(row + 2 * kPRowBytes) = L2;
-            *reinterpret_cast<uint32_t*>(row + 3 * kPRowBytes) = L3;
-        }
+        write_limbs<LM>(s, pmat, col, grp);
         wave_lds_sync();
         v4i ap[LM];
 #pragma unroll
@@ -994,31 +1034,7 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
         for (int tile = tile0; tile <= tile_last; ++tile) step(tile, kbA, vbA, kbA, false);
     }
 
-    // Partial of each head: m, l = sum of P (all-ones column), centred accumulator. Lane (grp, col)
-    // holds every limb of head 4 pm + grp at coordinate 16 nt + col; the all-ones column is col 0.
-#pragma unroll
-    for (int pm = 0; pm < LM; ++pm) {
-        const int h = 4 * pm + grp;
-        const int o0 = __shfl(C[pm][8][0], lane & 48), o1 = __shfl(C[pm][8][1], lane & 48),
-                  o2 = __shfl(C[pm][8][2], lane & 48), o3 = __shfl(C[pm][8][3], lane & 48);
-        if (G % 4 == 0 || h < G) {
-            float* o = out + h * kPartStride;
-            if (col == 0) {
-                o[0] = mrun[pm];
-                o[1] = ((float)o0 + 256.f * (float)o1) + (65536.f * (float)o2 + 16777216.f * (float)o3);
-            }
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt) {
-                const int cc = 16 * nt + col;
-                if (nt < nv) {
-                    const int a0 = C[pm][nt][0] - hv * o0, a1 = C[pm][nt][1] - hv * o1, a2 = C[pm][nt][2] - hv * o2,
-                              a3 = C[pm][nt][3] - hv * o3;
-                    o[4 + cc] = cc < rv ? ((float)a0 + 256.f * (float)a1) + (65536.f * (float)a2 + 16777216.f * (float)a3)
-                                        : 0.f;
-                }
-            }
-        }
-    }
+    write_partial<G>(C, mrun, rv, hv, out, lane);
 }
 
 #undef KVC_SW_K
@@ -1090,482 +1106,6 @@ extern template __global__ void decode_partial_kernel<4>(DevSide, DevSide, const
 extern template __global__ void decode_partial_kernel<8>(DevSide, DevSide, const v4i*, const float4*, const int32_t*, int,
                                                          int, int, int, int, float*);
 #endif
-
-// ---------------------------------------------------------------- RoPE-aware partials
-
-// Keys are cached before the rotary position embedding (Sec. 5, scope), so a model with RoPE scores the
-// rotated query q' against each reconstructed key rotated at its own position; that depends on the
-// position and cannot be folded into a rank-space query. Per 64-token tile, in four blocks of 16 tokens:
-//  1. the block's centred K codes (c - 2^(b-1) + 1/2, exact in fp16) go to LDS, token-major;
-//  2. K^T (128 features x 16 tokens) = P_K^T Z^T on v_mfma_f32_16x16x32_f16, with P_K^T staged in LDS once
-//     per block of four wavefronts (the four context chunks of one unit share it); lane (col, kq) then
-//     holds features 16 rb + 4 kq + v of token col, so both members of every rotation pair (j, j + 64)
-//     sit in the same lane;
-//  3. each pair is rotated by the angle p theta_j, the position's turns computed as the tile's start
-//     (fp64, one frequency per lane) plus the offset inside the tile (fp32);
-//  4. the logits q' . K_rot on the same matrix instruction, K_rot split into fp16 hi + lo and q' permuted
-//     to the lane's feature order (the order of the k index of a dot product is free);
-// then the online softmax and the rank-space PV products exactly as in the partials kernel (int8 value
-// codes, probability limbs through LDS, int32 accumulators), writing the same partials, which the
-// combine kernel merges.
-constexpr int kRopeWaves = 4;
-constexpr int kPtPitch = 136;   // halves per feature row of the staged P_K^T (coordinates 0..127 + pad)
-constexpr int kZPitch = 136;    // halves per token row of a staged 16-token block of centred K codes
-constexpr int kRopeKTile = 8 * kD * 8;  // bytes of the widest K tile (r = 128, b = 8)
-constexpr int kRopeShared = kD * kPtPitch * 2 + 64 * 8;  // LDS shared by a block's wavefronts: P_K^T, E16
-constexpr int kRopeKChunks = kRopeKTile / 16 / 64;  // 16-byte loads per lane for one K tile
-// Blocks of 16 tokens processed together (their chains are independent and share each P_K^T operand
-// read): as many as the register file allows for the group size.
-__host__ __device__ constexpr int rope_blocks(int G) { return G <= 8 ? 2 : 1; }
-__host__ __device__ constexpr int rope_wave_lds(int G) {
-    return kRopeKTile + rope_blocks(G) * 16 * kZPitch * 2 + 16 * ((G + 3) / 4) * kPRowBytes + 64 * 4;
-}
-
-typedef _Float16 rp_h8 __attribute__((ext_vector_type(8)));
-typedef float rp_f4 __attribute__((ext_vector_type(4)));
-
-// Position of coordinate i in a staged row of centred K codes (and in the staged P_K^T): inside each
-// group of 16, coordinates m and m + 8 (m < 8) are neighbours, at 2 m and 2 m + 1, so that a pair of
-// codes converts to fp16 as one packed dword. The k order of the reconstruction's products is free.
-__host__ __device__ constexpr int zpos(int i) { return (i & ~15) | ((i & 7) << 1) | ((i >> 3) & 1); }
-
-// A 16-code field of one plane of width p (codes 16 g + m at bits p m), aligned at bit 0 in f[0 .. p / 2)
-// (f[0] low 16 bits for p = 1), as the pairs (m, m + 8): bits [0, p) and [16, 16 + p) of pr[m], the rest
-// of each half zero.
-template <int P>
-__device__ __forceinline__ void plane_pairs(const uint32_t (&f)[4], uint32_t (&pr)[8]) {
-    if constexpr (P == 1) {
-        const uint32_t y = (f[0] & 0xffu) | ((f[0] & 0xff00u) << 8);  // code m + 8 at bit 16 + m
-#pragma unroll
-        for (int m = 0; m < 8; ++m) pr[m] = (y >> m) & 0x00010001u;
-    } else if constexpr (P == 2) {
-#pragma unroll
-        for (int m = 0; m < 8; ++m) pr[m] = (f[0] >> (2 * m)) & 0x00030003u;
-    } else if constexpr (P == 4) {
-        const uint32_t y01 = perm(f[1], f[0], 0x05040100u), y23 = perm(f[1], f[0], 0x07060302u);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            pr[m] = (y01 >> (4 * m)) & 0x000f000fu;
-            pr[m + 4] = (y23 >> (4 * m)) & 0x000f000fu;
-        }
-    } else {
-#pragma unroll
-        for (int m = 0; m < 8; ++m)  // byte m % 4 of dwords m / 4 and m / 4 + 2, zero bytes between
-            pr[m] = perm(f[(m >> 2) + 2], f[m >> 2], 0x0c040c00u + 0x00010001u * (uint32_t)(m & 3));
-    }
-}
-
-// The fields of group g of token t of a K tile, aligned: a whole group's field of a plane of width p is
-// 16 p bits at bit p (1024 g + 16 t) of the plane; the tail group's (rho = r % 16 codes) starts at
-// bit p (1024 g16 + t rho) and is aligned with funnel shifts over five words (codes past rho are other
-// tokens' codes: finite, and they meet zero basis entries).
-template <int P>
-__device__ __forceinline__ void group_field(const uint8_t* __restrict__ plane, bool tail, int g, int g16, int rho, int t,
-                                            uint32_t (&f)[4]) {
-    if (!tail) {
-        const uint8_t* base = plane + P * (128 * g + 2 * t);
-        if constexpr (P == 1) {
-            f[0] = *reinterpret_cast<const uint16_t*>(base);
-        } else if constexpr (P == 2) {
-            f[0] = *reinterpret_cast<const uint32_t*>(base);
-        } else if constexpr (P == 4) {
-            const uint2 v2 = *reinterpret_cast<const uint2*>(base);
-            f[0] = v2.x; f[1] = v2.y;
-        } else {
-            const uint4 v4 = *reinterpret_cast<const uint4*>(base);
-            f[0] = v4.x; f[1] = v4.y; f[2] = v4.z; f[3] = v4.w;
-        }
-    } else {
-        const uint32_t bit0 = (uint32_t)(P * (1024 * g16 + t * rho));
-        const uint32_t* w = reinterpret_cast<const uint32_t*>(plane) + (bit0 >> 5);
-        const uint32_t d0 = w[0], d1 = w[1];
-        f[0] = funnel(d1, d0, bit0);
-        if constexpr (P >= 4) {
-            const uint32_t d2 = w[2];
-            f[1] = funnel(d2, d1, bit0);
-            if constexpr (P == 8) {
-                const uint32_t d3 = w[3], d4 = w[4];
-                f[2] = funnel(d3, d2, bit0);
-                f[3] = funnel(d4, d3, bit0);
-            }
-        }
-    }
-}
-
-// Stage the centred K codes (c - 2^(b-1) + 1/2, exact in fp16) of token t for the lane's two groups
-// 2 kq, 2 kq + 1 into its row of ZT, in zpos order: per code pair, the planes' bits are combined one
-// bit up, under the fp16 exponent of 512 (512 + c, exact: the spacing there is 1/2), and moved by one
-// packed add of -512 - 2^(b-1) + 1/2 (also exact).
-template <int B>
-__device__ __forceinline__ void rope_stage_codes(const uint8_t* __restrict__ ktile, int rk, int g16, int rho, int kq,
-                                                 int t, uint16_t* __restrict__ zrow) {
-    typedef _Float16 h2v __attribute__((ext_vector_type(2)));
-    const _Float16 sh = (_Float16)(-512.f - ((float)(1 << (B - 1)) - 0.5f));
-    const h2v sh2 = h2v{sh, sh};
-#pragma unroll
-    for (int gg = 0; gg < 2; ++gg) {
-        const int g = 2 * kq + gg;
-        const bool tail = g >= g16;
-        uint32_t pc[8];
-#pragma unroll
-        for (int m = 0; m < 8; ++m) pc[m] = 0u;
-#pragma unroll
-        for (int k = 0; k < n_planes(B); ++k) {
-            const int P = plane_w(B, k), SH = plane_sh(B, k), OFF = plane_off(B, k);
-            uint32_t f[4] = {0u, 0u, 0u, 0u}, pr[8];
-            const uint8_t* plane = ktile + 8 * rk * OFF;
-            if (P == 1) { group_field<1>(plane, tail, g, g16, rho, t, f); plane_pairs<1>(f, pr); }
-            else if (P == 2) { group_field<2>(plane, tail, g, g16, rho, t, f); plane_pairs<2>(f, pr); }
-            else if (P == 4) { group_field<4>(plane, tail, g, g16, rho, t, f); plane_pairs<4>(f, pr); }
-            else { group_field<8>(plane, tail, g, g16, rho, t, f); plane_pairs<8>(f, pr); }
-#pragma unroll
-            for (int m = 0; m < 8; ++m) pc[m] |= pr[m] << (SH + 1);
-        }
-        uint32_t hw[8];
-#pragma unroll
-        for (int m = 0; m < 8; ++m)
-            hw[m] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2v, pc[m] | 0x60006000u) + sh2);
-        *reinterpret_cast<uint4*>(zrow + 16 * g) = uint4{hw[0], hw[1], hw[2], hw[3]};
-        *reinterpret_cast<uint4*>(zrow + 16 * g + 8) = uint4{hw[4], hw[5], hw[6], hw[7]};
-    }
-}
-
-template <int G>
-__global__ __launch_bounds__(64 * kRopeWaves) void decode_rope_kernel(
-    DevSide K, DevSide V, const uint16_t* __restrict__ q, const int32_t* __restrict__ seq_len, int max_seq, int chunk,
-    int n_chunks, int v_cap_tiles, float log2_base, float* __restrict__ part) {
-    constexpr int LM = Shape<G>::LM;
-    extern __shared__ __attribute__((aligned(16))) uint8_t rope_sm[];
-    const int u = blockIdx.y, wv = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    const int col = lane & 15, kq = lane >> 4, grp = kq;
-    const int rk = uni(K.r[u]), bk = uni(K.b[u]);
-    uint16_t* PT = reinterpret_cast<uint16_t*>(rope_sm);  // [128 features][kPtPitch]
-    float2* E16 = reinterpret_cast<float2*>(rope_sm + kRopeShared - 64 * 8);  // [64 pairs] rotation by 16 positions
-    if (threadIdx.x < 64) {
-        // cos, sin of the rotation of pair j by 16 positions (turns reduced in fp64)
-        const int j = threadIdx.x;
-        const double w = exp2(-(double)j / 64.0 * (double)log2_base) * 0.15915494309189535;
-        const float t16 = (float)(6.283185307179586 * (16.0 * w - floor(16.0 * w)));
-        E16[j] = float2{cosf(t16), sinf(t16)};
-    }
-    {
-        // stage P_K^T: zero it (coordinates past the rank take part in the last 32-wide k-step), then
-        // transpose the basis rows in
-        for (int e = threadIdx.x; e < kD * kPtPitch / 8; e += 64 * kRopeWaves)
-            reinterpret_cast<uint4*>(PT)[e] = uint4{0u, 0u, 0u, 0u};
-        __syncthreads();
-        const uint16_t* __restrict__ P = K.basis + K.basis_off[u];
-        for (int e = threadIdx.x; e < rk * (kD / 8); e += 64 * kRopeWaves) {
-            const int i = e / (kD / 8), f0 = 8 * (e % (kD / 8));
-            const uint4 w = reinterpret_cast<const uint4*>(P + (int64_t)i * kD)[f0 / 8];
-            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-            for (int k = 0; k < 8; ++k) PT[(f0 + k) * kPtPitch + zpos(i)] = (uint16_t)(ww[k >> 1] >> (16 * (k & 1)));
-        }
-        __syncthreads();
-    }
-    const int c = blockIdx.x * kRopeWaves + wv;
-    if (c >= n_chunks) return;  // no block-wide barrier follows
-    constexpr int NB = rope_blocks(G);
-    uint8_t* wbase = rope_sm + kRopeShared + wv * rope_wave_lds(G);
-    uint8_t* KS = wbase;                                               // the K tile being processed
-    uint16_t* ZT = reinterpret_cast<uint16_t*>(wbase + kRopeKTile);     // [NB blocks][16 tokens][kZPitch]
-    uint8_t* pmat = wbase + kRopeKTile + NB * 16 * kZPitch * 2;        // [16 LM][kPRowBytes]
-    float* rho0 = reinterpret_cast<float*>(pmat + 16 * LM * kPRowBytes);  // [64] tile start, turns
-
-    int T = uni(seq_len[u]);
-    T = T < 0 ? 0 : (T > max_seq ? max_seq : T);
-    const int start = uni(c * chunk);
-    const int end = uni(min(T, start + chunk));
-    float* __restrict__ out = part + ((int64_t)u * n_chunks + c) * G * kPartStride;
-    if (start >= end) {
-        if (lane < G) { out[lane * kPartStride] = -INFINITY; out[lane * kPartStride + 1] = 0.f; }
-        return;
-    }
-    const int rv = uni(V.r[u]), bv = uni(V.b[u]);
-    const int hv = bv == 8 ? 0 : (1 << (bv - 1));
-    const int nks = (rk + 31) >> 5, nv = (rv + 15) >> 4, g16 = rk >> 4, rho = rk & 15;
-    const int ktb = 8 * rk * bk, vtb = 8 * rv * bv;
-    const int tile0 = uni(start / kTile), tile_last = uni((end - 1) / kTile);
-    const uint8_t* kstream = uni(K.codes + K.code_off[u]);
-    const uint8_t* vstream = uni(V.codes + V.code_off[u]);
-    v_cap_tiles = uni(v_cap_tiles);
-    auto v_rs = [&](int t) {
-        const bool ok = t <= tile_last;
-        return __builtin_amdgcn_make_buffer_rsrc((void*)(vstream + (int64_t)t * vtb), (short)0,
-                                                 ok ? (v_cap_tiles - t) * vtb : 0, kRsrcWord3);
-    };
-    // K tile t as one range-checked descriptor (reads past the tile return zero; none past the chunk)
-    auto k_rs = [&](int t) {
-        return __builtin_amdgcn_make_buffer_rsrc((void*)(kstream + (int64_t)t * ktb), (short)0, t <= tile_last ? ktb : 0,
-                                                 kRsrcWord3);
-    };
-    // the K tile's bytes, 16 per lane and load, in flight one tile ahead
-    v4u kpf[kRopeKChunks];
-    auto k_fetch = [&](int t) {
-        const auto rs = k_rs(t);
-#pragma unroll
-        for (int m = 0; m < kRopeKChunks; ++m) kpf[m] = __builtin_amdgcn_raw_buffer_load_b128(rs, 16 * (lane + 64 * m), 0, 0);
-    };
-    // q' as the logits' A operand: row = head (col), k-step ks, element e <-> feature 16 (2 ks + e / 4) + 4 kq + e % 4
-    rp_h8 qa[4];
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int f = 16 * (2 * ks + (e >> 2)) + 4 * kq + (e & 3);
-            qa[ks][e] = col < G ? __builtin_bit_cast(_Float16, q[((int64_t)u * G + col) * kD + f]) : (_Float16)0.f;
-        }
-    // rotation frequencies of the lane's pairs j = 16 rb + 4 kq + v (rb < 4), in turns per position
-    float om[4][4];
-#pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int j = 16 * rb + 4 * kq + v;
-            om[rb][v] = (float)(exp2(-(double)j / 64.0 * (double)log2_base) * 0.15915494309189535);
-        }
-    const double om_lane = exp2(-(double)lane / 64.0 * (double)log2_base) * 0.15915494309189535;  // frequency j = lane
-    const float scale = K.delta[u] * 1.4426950408889634f * 0.08838834764831845f;  // step_K log2(e) / sqrt(128)
-
-    float mrun[4];  // running max of heads 4 kq + v (log2 domain), replicated over the group's 16 lanes
-#pragma unroll
-    for (int v = 0; v < 4; ++v) mrun[v] = -INFINITY;
-    for (int k = lane; k < 16 * LM * kPRowBytes / 4; k += 64) reinterpret_cast<uint32_t*>(pmat)[k] = 0u;
-    v4i C[LM][9];
-#pragma unroll
-    for (int pm = 0; pm < LM; ++pm)
-#pragma unroll
-        for (int nt = 0; nt < 9; ++nt) C[pm][nt] = v4i{0, 0, 0, 0};
-    const uint32_t one = col == 0 ? 0x01010101u : 0u;
-    const v4i ones = v4i{(int)one, (int)one, (int)one, (int)one};
-    uint32_t vb[kVBufWords];
-#pragma unroll
-    for (int k = 0; k < kVBufWords; ++k) vb[k] = 0u;
-    const uint32_t LV = (uint32_t)(4 * col + grp), VA = v_lane_adj(rv, col, grp);
-    {
-        const auto vrs = v_rs(tile0);
-        KVC_SWITCH_B(bv, (v_prefetch<B_, 8>(vb, vrs, rv, LV, VA)));
-    }
-    k_fetch(tile0);
-
-    for (int tile = tile0; tile <= tile_last; ++tile) {
-        // the K tile to LDS, then the next tile's loads go out
-#pragma unroll
-        for (int m = 0; m < kRopeKChunks; ++m)
-            if (16 * (lane + 64 * m) < ktb) *reinterpret_cast<v4u*>(KS + 16 * (lane + 64 * m)) = kpf[m];
-        k_fetch(tile + 1);
-        const int tok0 = tile * kTile;
-        // Opaque per-tile copies of the widths, ranks and lane offsets: the addresses every width's branch
-        // derives from them are recomputed inside the loop, not hoisted and kept live for all widths.
-        int rkt = rk, bkt = bk, rvt = rv, bvt = bv, nvt = nv, g16t = g16, rhot = rho, nkst = nks;
-        uint32_t LVt = LV, VAt = VA;
-        int colt = col, kqt = kq;
-        asm volatile("" : "+v"(LVt), "+v"(VAt), "+v"(colt), "+v"(kqt));
-        asm volatile("" : "+s"(rkt), "+s"(bkt), "+s"(rvt), "+s"(bvt), "+s"(nvt), "+s"(g16t), "+s"(rhot), "+s"(nkst));
-        const uint8_t* ktile = KS;
-        {
-            // turns of the tile's first position for frequency j = lane (fp64, then reduced)
-            const double t0 = (double)tok0 * om_lane;
-            rho0[lane] = (float)(t0 - floor(t0));
-        }
-        // rotation of the lane's token in block 0 (position tok0 + col) for each of its pairs, as cos, sin;
-        // block tb's follows by tb rotations of 16 positions
-        float wc[4][4], ws[4][4];
-        wave_lds_sync();  // rho0 written above
-#pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float tr = fmaf((float)col, om[rb][v], rho0[16 * rb + 4 * kq + v]);
-                tr -= floorf(tr);
-                wc[rb][v] = __cosf(6.283185307179586f * tr);
-                ws[rb][v] = __sinf(6.283185307179586f * tr);
-            }
-        float s[4][4];  // [token block][head v], log2 domain
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) s[a][v] = -INFINITY;
-        // The tile's four blocks of 16 tokens in groups of NB (tb = NB tp + h): the blocks' chains are
-        // independent and share each P_K^T operand read.
-#pragma unroll 1
-        for (int tp = 0; tp < 4 / NB; ++tp) {
-#pragma unroll
-            for (int h = 0; h < NB; ++h) {
-                // stage the centred codes of tokens 16 tb .. 16 tb + 15: lane (token col, part kq) takes
-                // coordinates 32 kq .. 32 kq + 31 (zero past the rank, within the 32-wide k-steps)
-                const int t = 16 * (NB * tp + h) + colt;
-                KVC_SWITCH_B(bkt, (rope_stage_codes<B_>(ktile, rkt, g16t, rhot, kqt, t, ZT + (16 * h + colt) * kZPitch)));
-            }
-            wave_lds_sync();
-            // K^T blocks: rows 16 rb + 4 kq + v, column token col
-            rp_f4 Cr[NB][8];
-#pragma unroll
-            for (int h = 0; h < NB; ++h)
-#pragma unroll
-                for (int rb = 0; rb < 8; ++rb) Cr[h][rb] = rp_f4{0.f, 0.f, 0.f, 0.f};
-            for (int ks = 0; ks < nkst; ++ks) {
-                rp_h8 bz[NB];
-#pragma unroll
-                for (int h = 0; h < NB; ++h)
-                    bz[h] = *reinterpret_cast<const rp_h8*>(ZT + (16 * h + col) * kZPitch + 32 * ks + 8 * kq);
-#pragma unroll
-                for (int rb = 0; rb < 8; ++rb) {
-                    const rp_h8 ap = *reinterpret_cast<const rp_h8*>(PT + (16 * rb + col) * kPtPitch + 32 * ks + 8 * kq);
-#pragma unroll
-                    for (int h = 0; h < NB; ++h) Cr[h][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ap, bz[h], Cr[h][rb], 0, 0, 0);
-                }
-            }
-            wave_lds_sync();  // ZT is rewritten by the next group of blocks
-#pragma unroll
-            for (int h = 0; h < NB; ++h) {
-                const int tb = NB * tp + h;
-                // rotate each pair (j, j + 64) of token 16 tb + col at its position, then advance the
-                // rotation by 16 positions for the next block
-#pragma unroll
-                for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float cs = wc[rb][v], sn = ws[rb][v];
-                        const float a = Cr[h][rb][v], b = Cr[h][rb + 4][v];
-                        Cr[h][rb][v] = fmaf(a, cs, -b * sn);
-                        Cr[h][rb + 4][v] = fmaf(a, sn, b * cs);
-                        const float2 e = E16[16 * rb + 4 * kq + v];
-                        wc[rb][v] = fmaf(cs, e.x, -sn * e.y);
-                        ws[rb][v] = fmaf(cs, e.y, sn * e.x);
-                    }
-                // logits: sum over features of q' times (hi + lo) of the rotated key
-                rp_f4 S = rp_f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks) {
-                    rp_h8 bh, bl;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float x = Cr[h][2 * ks + (e >> 2)][e & 3];
-                        const _Float16 hx = (_Float16)x;
-                        bh[e] = hx;
-                        bl[e] = (_Float16)(x - (float)hx);
-                    }
-                    S = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[ks], bh, S, 0, 0, 0);
-                    S = __builtin_amdgcn_mfma_f32_16x16x32_f16(qa[ks], bl, S, 0, 0, 0);
-                }
-                const bool valid_tok = tok0 + 16 * tb + col < end;
-#pragma unroll
-                for (int a = 0; a < 4; ++a)  // s[tb] without a run-time register index
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (a == tb) s[a][v] = (valid_tok && 4 * kq + v < G) ? S[v] * scale : -INFINITY;
-            }
-        }
-
-        // ---- online softmax of the tile: heads 4 kq + v live in the 16 lanes of group kq
-        float mx[4];
-        bool raise = false;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            mx[v] = row_max(fmaxf(fmaxf(s[0][v], s[1][v]), fmaxf(s[2][v], s[3][v])));
-            raise = raise || (mx[v] > -INFINITY && (mrun[v] == -INFINITY || mx[v] - mrun[v] > kLazy));
-        }
-        if (__any(raise)) {
-            float alpha[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                alpha[v] = 1.f;
-                if (mx[v] > -INFINITY && (mrun[v] == -INFINITY || mx[v] - mrun[v] > kLazy)) {
-                    alpha[v] = mrun[v] == -INFINITY ? 0.f : exp2f(mrun[v] - mx[v]);
-                    mrun[v] = mx[v];
-                }
-            }
-            // accumulators of head 4 pm + grp: its factor lives in lane 16 pm, element grp
-#pragma unroll
-            for (int pm = 0; pm < LM; ++pm) {
-                float al = 1.f;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float t = __shfl(alpha[v], 16 * pm);
-                    if (grp == v) al = t;
-                }
-                if (al != 1.f) {
-                    const double a = (double)al;
-#pragma unroll
-                    for (int nt = 0; nt < 9; ++nt) {
-                        const double vv = ((double)C[pm][nt][0] + 256.0 * (double)C[pm][nt][1]) +
-                                          (65536.0 * (double)C[pm][nt][2] + 16777216.0 * (double)C[pm][nt][3]);
-                        const double vs = rint(vv * a);
-                        const double c3 = floor(vs * (1.0 / 16777216.0));
-                        const double r3 = vs - 16777216.0 * c3;
-                        const double c2 = floor(r3 * (1.0 / 65536.0));
-                        const double r2 = r3 - 65536.0 * c2;
-                        const double c1 = floor(r2 * (1.0 / 256.0));
-                        C[pm][nt][3] = (int)c3;
-                        C[pm][nt][2] = (int)c2;
-                        C[pm][nt][1] = (int)c1;
-                        C[pm][nt][0] = (int)(r2 - 256.0 * c1);
-                    }
-                }
-            }
-        }
-        // ---- probability limbs of heads 4 kq + v, token 16 tb + col: row 16 kq + 4 v + limb, byte = token
-        if (kq < LM) {
-#pragma unroll
-            for (int tb = 0; tb < 4; ++tb)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float pr = s[tb][v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s[tb][v] - mrun[v]);
-                    const uint32_t P = (uint32_t)fmaf(pr, kPScale, kPBias);
-                    uint8_t* row = pmat + (16 * kq + 4 * v) * kPRowBytes + 16 * tb + col;
-                    row[0] = (uint8_t)((P & 255u) ^ 0x80u);
-                    row[kPRowBytes] = (uint8_t)(((P >> 8) & 255u) ^ 0x80u);
-                    row[2 * kPRowBytes] = (uint8_t)(((P >> 16) & 255u) ^ 0x80u);
-                    row[3 * kPRowBytes] = (uint8_t)(P >> 24);
-                }
-        }
-        wave_lds_sync();
-        v4i ap[LM];
-#pragma unroll
-        for (int pm = 0; pm < LM; ++pm)
-            ap[pm] = *reinterpret_cast<const v4i*>(pmat + (16 * pm + col) * kPRowBytes + 16 * grp);
-        {
-            const auto vrs = v_rs(tile), vrs_n = v_rs(tile + 1);
-            KVC_SWITCH_B(bvt, (v_tile<B_, LM, 8>(vb, vrs, vrs_n, rvt, LVt, VAt, ap, C)));
-        }
-#pragma unroll
-        for (int pm = 0; pm < LM; ++pm) C[pm][8] = mfma_i8(ap[pm], ones, C[pm][8]);
-        wave_lds_sync();  // pmat and rho0 are rewritten by the next tile
-    }
-
-    // partials: m of head 4 pm + grp (lane 16 pm, element grp), l and the centred accumulator
-#pragma unroll
-    for (int pm = 0; pm < LM; ++pm) {
-        const int h = 4 * pm + grp;
-        float mh = -INFINITY;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float t = __shfl(mrun[v], 16 * pm);
-            if (grp == v) mh = t;
-        }
-        const int o0 = __shfl(C[pm][8][0], lane & 48), o1 = __shfl(C[pm][8][1], lane & 48),
-                  o2 = __shfl(C[pm][8][2], lane & 48), o3 = __shfl(C[pm][8][3], lane & 48);
-        if (G % 4 == 0 || h < G) {
-            float* o = out + h * kPartStride;
-            if (col == 0) {
-                o[0] = mh;
-                o[1] = ((float)o0 + 256.f * (float)o1) + (65536.f * (float)o2 + 16777216.f * (float)o3);
-            }
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt) {
-                const int cc = 16 * nt + col;
-                if (nt < nv) {
-                    const int a0 = C[pm][nt][0] - hv * o0, a1 = C[pm][nt][1] - hv * o1, a2 = C[pm][nt][2] - hv * o2,
-                              a3 = C[pm][nt][3] - hv * o3;
-                    o[4 + cc] = cc < rv ? ((float)a0 + 256.f * (float)a1) + (65536.f * (float)a2 + 16777216.f * (float)a3)
-                                        : 0.f;
-                }
-            }
-        }
-    }
-}
 
 // ---------------------------------------------------------------- combine
 
@@ -1700,7 +1240,7 @@ inline int combine_waves(int G, int n_chunks, int U, int ncu) {
 
 // Combine launch with cw (a power of two that combine_waves chose for this G) wavefronts per block.
 template <int G>
-void launch_combine(int cw, dim3 grid, dim3 blk, size_t smem, hipStream_t st, const DevSide& V, int n_chunks,
+void launch_combine_g(int cw, dim3 grid, dim3 blk, size_t smem, hipStream_t st, const DevSide& V, int n_chunks,
                     const float* part, float* out) {
     switch (cw) {
         case 8:
@@ -1876,6 +1416,20 @@ extern "C" size_t kvc_decode_attn_workspace(const kvc_stream_desc* k, const kvc_
 namespace kvc {
 namespace {
 
+// Combine launch for U units of n_chunks partials each.
+void launch_combine(int G, int U, const DevSide& V, int n_chunks, const float* part, float* out, hipStream_t st) {
+    const int cw = combine_waves(G, n_chunks, U, device_cus());
+    const dim3 cblk(64 * cw);
+    const size_t csm = (size_t)cw * G * kPartStride * 4;
+    switch (G) {
+        case 1: launch_combine_g<1>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+        case 2: launch_combine_g<2>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+        case 4: launch_combine_g<4>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+        case 8: launch_combine_g<8>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+        default: launch_combine_g<16>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+    }
+}
+
 // The new token of a fused decode step (none for a plain decode call).
 struct StepAppend {
     const uint16_t* xk = nullptr;
@@ -1918,16 +1472,7 @@ int decode_launch(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
         default: e = launch_partials<16>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
     }
     if (e) return e;
-    const int cw = combine_waves(G, L.n_chunks, U, device_cus());
-    const dim3 cblk(64 * cw);
-    const size_t csm = (size_t)cw * G * kPartStride * 4;
-    switch (G) {
-        case 1: launch_combine<1>(cw, dim3(U), cblk, csm, st, V, L.n_chunks, part, out); break;
-        case 2: launch_combine<2>(cw, dim3(U), cblk, csm, st, V, L.n_chunks, part, out); break;
-        case 4: launch_combine<4>(cw, dim3(U), cblk, csm, st, V, L.n_chunks, part, out); break;
-        case 8: launch_combine<8>(cw, dim3(U), cblk, csm, st, V, L.n_chunks, part, out); break;
-        default: launch_combine<16>(cw, dim3(U), cblk, csm, st, V, L.n_chunks, part, out); break;
-    }
+    launch_combine(G, U, V, L.n_chunks, part, out, st);
     return check_launch("kvc_decode_attn");
 }
 
@@ -2012,32 +1557,6 @@ extern "C" int kvc_decode_step(const kvc_stream_desc* k, const kvc_stream_desc* 
     return decode_launch(k, v, q, G, seq_len, max_seq_len, out, ws, L, stream, app);
 }
 
-namespace kvc {
-namespace {
-
-template <int G>
-int launch_rope(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, const int32_t* seq_len,
-                int32_t max_seq_len, float log2_base, float* out, const WsLayout& L, float* part, hipStream_t st) {
-    const size_t smem = (size_t)kRopeShared + (size_t)kRopeWaves * rope_wave_lds(G);
-    if (smem > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void*)decode_rope_kernel<G>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return set_error(KVC_EDEVICE, "hipFuncSetAttribute: %s", hipGetErrorString(e));
-    }
-    const int U = k->n_units;
-    const int vct = (v->capacity + kTile - 1) / kTile;
-    const DevSide K = dev_side(k), V = dev_side(v);
-    hipLaunchKernelGGL(decode_rope_kernel<G>, dim3((L.n_chunks + kRopeWaves - 1) / kRopeWaves, U),
-                       dim3(64 * kRopeWaves), smem, st, K, V, q, seq_len, max_seq_len, L.chunk, L.n_chunks, vct,
-                       log2_base, part);
-    const int cw = combine_waves(G, L.n_chunks, U, device_cus());
-    launch_combine<G>(cw, dim3(U), dim3(64 * cw), (size_t)cw * G * kPartStride * 4, st, V, L.n_chunks, part, out);
-    return check_launch("kvc_decode_attn_rope");
-}
-
-}  // namespace
-}  // namespace kvc
-
 extern "C" int kvc_decode_attn_rope(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, int32_t G,
                                     const int32_t* seq_len, int32_t max_seq_len, float rope_base, float* out,
                                     void* ws, size_t ws_bytes, void* stream) {
@@ -2053,15 +1572,12 @@ extern "C" int kvc_decode_attn_rope(const kvc_stream_desc* k, const kvc_stream_d
     if ((int64_t)ws_bytes < L.total)
         return set_error(KVC_ENOSPACE, "kvc_decode_attn_rope: workspace %zu < %lld bytes", ws_bytes, (long long)L.total);
     float* part = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + L.part);
-    const float lb = (float)std::log2((double)rope_base);
-    hipStream_t st = (hipStream_t)stream;
-    switch (G) {
-        case 1: return launch_rope<1>(k, v, q, seq_len, max_seq_len, lb, out, L, part, st);
-        case 2: return launch_rope<2>(k, v, q, seq_len, max_seq_len, lb, out, L, part, st);
-        case 4: return launch_rope<4>(k, v, q, seq_len, max_seq_len, lb, out, L, part, st);
-        case 8: return launch_rope<8>(k, v, q, seq_len, max_seq_len, lb, out, L, part, st);
-        default: return launch_rope<16>(k, v, q, seq_len, max_seq_len, lb, out, L, part, st);
-    }
+    int n_chunks = L.n_chunks;  // the workspace holds at most that many partials per unit
+    if (int e = launch_rope_partials(k, v, q, G, seq_len, max_seq_len, std::log2((double)rope_base), L.stage_bytes, part, &n_chunks,
+                                     (hipStream_t)stream))
+        return e;
+    launch_combine(G, k->n_units, dev_side(v), n_chunks, part, out, (hipStream_t)stream);
+    return check_launch("kvc_decode_attn_rope");
 }
 
 extern "C" int kvc_decode_attn_noalloc(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q,

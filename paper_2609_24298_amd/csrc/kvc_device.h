@@ -169,4 +169,10 @@ inline int check_launch(const char* what) {
     return KVC_OK;
 }
 
+// Partials of the RoPE-aware decode (kvc_rope.hip): chooses a chunk count of at most *n_chunks and returns
+// it there; part holds [unit][chunk][head] partials as the rank-space decode writes them. stage_bytes: LDS
+// of a staged tail K-step.
+int launch_rope_partials(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, int32_t G, const int32_t* seq_len,
+                         int32_t max_seq_len, double log2_base, int stage_bytes, float* part, int* n_chunks, hipStream_t st);
+
 }  // namespace kvc
