@@ -40,7 +40,7 @@ def build(verbose: bool = True) -> str:
     objs = [host_o]
     # the HIP sources compile in parallel (the two decode partials units take most of the time)
     procs = []
-    for src in ("kvc_decode_g4.hip", "kvc_decode_g8.hip", "kvc_decode.hip", "kvc_rope_g4.hip", "kvc_rope_g8.hip", "kvc_rope_g16.hip",
+    for src in ("kvc_decode_g4.hip", "kvc_decode_g8.hip", "kvc_decode.hip", "kvc_rope_g4.hip", "kvc_rope_g8.hip",
                 "kvc_rope.hip", "kvc_recon.hip", "kvc_kernels.hip", "kvc_calib.hip"):
         o = os.path.join(BUILD, src.replace(".hip", ".o"))
         cmd = [hipcc, "-std=c++17", "-O3", "-fPIC", f"--offload-arch={ARCH}", "-ffp-contract=fast",

@@ -78,11 +78,19 @@ __device__ __forceinline__ void plane_pairs(const Fld& f, bool hi, uint32_t (&pr
     }
 }
 
+// Two fp16 exponents of 512, in a register the compiler does not know: masking a code pair and setting its
+// exponents is then one instruction (it cannot hold two 32-bit literals).
+__device__ __forceinline__ uint32_t exp512() {
+    uint32_t e = 0x60006000u;
+    asm volatile("" : "+v"(e));
+    return e;
+}
+
 // A token's 16 codes of a coordinate group as two fp16 operand fragments (matrix steps 2 ks and
 // 2 ks + 1): per pair, the code's bits one up under the fp16 exponent of 512 give 512 + c (exact, the
 // spacing there is 1/2), and one packed add of -512 - 2^(b-1) + 1/2 the centred code (exact).
 template <int B>
-__device__ __forceinline__ void k_pairs(const Fld (&f)[3], bool hi, rc_h8 (&z)[2]) {
+__device__ __forceinline__ void k_pairs(const Fld (&f)[3], bool hi, uint32_t e512, rc_h8 (&z)[2]) {
     const _Float16 sh = (_Float16)(-512.f - ((float)(1 << (B - 1)) - 0.5f));
     const rc_h2 sh2 = rc_h2{sh, sh};
     uint32_t pc[8];
@@ -101,7 +109,7 @@ __device__ __forceinline__ void k_pairs(const Fld (&f)[3], bool hi, rc_h8 (&z)[2
     }
     uint32_t hw[8];
 #pragma unroll
-    for (int m = 0; m < 8; ++m) hw[m] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(rc_h2, pc[m] | 0x60006000u) + sh2);
+    for (int m = 0; m < 8; ++m) hw[m] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(rc_h2, pc[m] | e512) + sh2);
 #pragma unroll
     for (int h = 0; h < 2; ++h)
         z[h] = __builtin_bit_cast(rc_h8, v4u{hw[4 * h], hw[4 * h + 1], hw[4 * h + 2], hw[4 * h + 3]});

@@ -66,6 +66,7 @@ __device__ __forceinline__ void rec_tile_k(const uint16_t* __restrict__ PT, uint
     const int col = lane & 15, grp = lane >> 4;
     const int g16 = r >> 4, rho = r & 15, ks_t = rho ? (g16 >> 2) : 2;
     constexpr int W0 = k_step_words(B);
+    const uint32_t e512 = exp512();
     uint32_t w[NK * W0];
 #pragma unroll
     for (int ks = 0; ks < NK; ++ks) {
@@ -94,10 +95,10 @@ __device__ __forceinline__ void rec_tile_k(const uint16_t* __restrict__ PT, uint
                 rc_h8 zz[2];
                 if (ks == ks_t) {
                     k_fields_staged<B>(stage, xb + (sp + h) * xs, f);
-                    k_pairs<B>(f, false, zz);
+                    k_pairs<B>(f, false, e512, zz);
                 } else {
                     k_fields_direct<B>(w + ks * W0, sp + h, f);
-                    k_pairs<B>(f, ((sp + h) & 1) != 0, zz);
+                    k_pairs<B>(f, ((sp + h) & 1) != 0, e512, zz);
                 }
                 z[h][2 * ks] = zz[0];
                 z[h][2 * ks + 1] = zz[1];

@@ -34,10 +34,10 @@ namespace kvc {
 
 template <int G> struct RopeShape {
     static constexpr int LM = Shape<G>::LM;
-    static constexpr int W = G <= 8 ? 2 : 1;       // wavefronts per SIMD the register budget is cut for
-    static constexpr int NB = 1;     // token blocks per read of a P_K^T operand
+    static constexpr int W = 2;   // wavefronts per SIMD the register budget is cut for
+    static constexpr int NB = 1;  // token blocks per read of a P_K^T operand (two spill: 3-20 % slower)
     // Wavefronts per block (they share P_K^T and the query table): two blocks of four per CU, or one of
-    // eight for G = 8, whose query table does not leave room for two, and four for G = 16 (one per SIMD).
+    // eight for G = 8, whose query table does not leave room for two.
     static constexpr int kWaves = G == 8 ? 8 : 4;
     static constexpr int kPt = kD * kBtPitch * 2;                    // P_K^T
     static constexpr int kKey = 4 * 64 * 8 * 4;                      // cos, sin of 4 col positions: [rb][2][lane] float4
@@ -46,20 +46,27 @@ template <int G> struct RopeShape {
     static constexpr int kWave = 16 * LM * kPRowBytes + 64 * 8;      // probability limbs, the tile's cos, sin (+ staged K-step)
 };
 
-// hi + lo fp16 halves of x in element e of two operand fragments.
-__device__ __forceinline__ void split_h(float x, rc_h8& hi, rc_h8& lo, int e) {
+// K-steps of a k_mode, and the one that holds the tail group (2: none).
+__host__ __device__ constexpr int k_steps(int km) { return km < 2 ? 2 : 1; }
+__host__ __device__ constexpr int k_tail(int km) { return km == 1 ? 1 : (km == 3 ? 0 : 2); }
+
+// hi + lo fp16 halves of x in element e of two operand fragments. m1 is -1 in a register the compiler does
+// not know: x - hi stays one mixed-precision multiply-add that reads the half, not a conversion and a
+// subtraction.
+__device__ __forceinline__ void split_h(float x, float m1, rc_h8& hi, rc_h8& lo, int e) {
     const _Float16 h = (_Float16)x;
     hi[e] = h;
-    lo[e] = (_Float16)fmaf((float)h, -1.f, x);
+    lo[e] = (_Float16)fmaf((float)h, m1, x);
 }
 
 // Logits of a tile: s[lm][st] (log2 domain, plus off) of the lane's tokens 4 col + st and head 4 lm + grp.
 // kb: the tile's K fields (NK K-steps).
-template <int G, int B, int NK>
-__device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], const uint8_t* __restrict__ stage, int ks_t, uint32_t xb,
+template <int G, int B, int KM>
+__device__ __forceinline__ void rope_logits(const uint32_t (&kb)[k_steps(KM) * 2 * B], const uint8_t* __restrict__ stage, uint32_t xb,
                                             uint32_t xs, const rc_h8 (&ah)[Shape<G>::LM][4], const rc_h8 (&al)[Shape<G>::LM][4],
-                                            const float (&qs)[Shape<G>::LM], const float (&off)[Shape<G>::LM],
+                                            float m1, uint32_t e512, const float (&qs)[Shape<G>::LM], const float (&off)[Shape<G>::LM],
                                             float (&s)[Shape<G>::LM][4], int lane) {
+    constexpr int NK = k_steps(KM), ks_t = k_tail(KM);
     constexpr int LM = Shape<G>::LM, NB = RopeShape<G>::NB, W0 = k_step_words(B);
     const int col = lane & 15, grp = lane >> 4;
 #pragma unroll
@@ -83,10 +90,10 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], co
                 Fld f[3];
                 if (ks == ks_t) {
                     k_fields_staged<B>(stage, xb + (sp + h) * xs, f);
-                    k_pairs<B>(f, false, z[h]);
+                    k_pairs<B>(f, false, e512, z[h]);
                 } else {
                     k_fields_direct<B>(kb + ks * W0, sp + h, f);
-                    k_pairs<B>(f, ((sp + h) & 1) != 0, z[h]);
+                    k_pairs<B>(f, ((sp + h) & 1) != 0, e512, z[h]);
                 }
             }
 #pragma unroll
@@ -100,13 +107,14 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], co
         }
         // rotation by 4 col positions, the split, and the logits, two rotation pair groups at a time
         // (matrix step ks takes features 32 ks + ..: pair groups rb = 2 ks, 2 ks + 1 and their partners)
-        rc_f4 S[NB][LM][3];
+        constexpr int NS = LM == 1 ? 3 : 1;  // one accumulator per product, or one in all (registers)
+        rc_f4 S[NB][LM][NS];
 #pragma unroll
         for (int h = 0; h < NB; ++h)
 #pragma unroll
             for (int lm = 0; lm < LM; ++lm)
 #pragma unroll
-                for (int t = 0; t < 3; ++t) S[h][lm][t] = rc_f4{0.f, 0.f, 0.f, 0.f};
+                for (int t = 0; t < NS; ++t) S[h][lm][t] = rc_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             float4 cs[2][2];
@@ -124,17 +132,17 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], co
                     for (int v = 0; v < 4; ++v) {
                         const float c = (v & 1) ? cs[r2][v >> 1].z : cs[r2][v >> 1].x, sn = (v & 1) ? cs[r2][v >> 1].w : cs[r2][v >> 1].y;
                         const float a = Cr[h][2 * ks + r2][v], b = Cr[h][2 * ks + r2 + 4][v];
-                        split_h(fmaf(a, c, -b * sn), xh, xl, 4 * r2 + v);
-                        split_h(fmaf(a, sn, b * c), yh, yl, 4 * r2 + v);
+                        split_h(fmaf(a, c, -b * sn), m1, xh, xl, 4 * r2 + v);
+                        split_h(fmaf(a, sn, b * c), m1, yh, yl, 4 * r2 + v);
                     }
 #pragma unroll
                 for (int lm = 0; lm < LM; ++lm) {
                     S[h][lm][0] = mfma_h(ah[lm][ks], xh, S[h][lm][0]);
-                    S[h][lm][1] = mfma_h(ah[lm][ks], xl, S[h][lm][1]);
-                    S[h][lm][2] = mfma_h(al[lm][ks], xh, S[h][lm][2]);
+                    S[h][lm][1 % NS] = mfma_h(ah[lm][ks], xl, S[h][lm][1 % NS]);
+                    S[h][lm][2 % NS] = mfma_h(al[lm][ks], xh, S[h][lm][2 % NS]);
                     S[h][lm][0] = mfma_h(ah[lm][ks + 2], yh, S[h][lm][0]);
-                    S[h][lm][1] = mfma_h(ah[lm][ks + 2], yl, S[h][lm][1]);
-                    S[h][lm][2] = mfma_h(al[lm][ks + 2], yh, S[h][lm][2]);
+                    S[h][lm][1 % NS] = mfma_h(ah[lm][ks + 2], yl, S[h][lm][1 % NS]);
+                    S[h][lm][2 % NS] = mfma_h(al[lm][ks + 2], yh, S[h][lm][2 % NS]);
                 }
             }
         }
@@ -142,7 +150,8 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], co
         for (int h = 0; h < NB; ++h)
 #pragma unroll
             for (int lm = 0; lm < LM; ++lm)
-                s[lm][sp + h] = fmaf(S[h][lm][0][sp + h] + (S[h][lm][1][sp + h] + S[h][lm][2][sp + h]), qs[lm], off[lm]);
+                s[lm][sp + h] = fmaf(NS == 3 ? S[h][lm][0][sp + h] + (S[h][lm][1 % NS][sp + h] + S[h][lm][2 % NS][sp + h]) : S[h][lm][0][sp + h],
+                                     qs[lm], off[lm]);
     }
 }
 
@@ -161,12 +170,16 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[NK * 2 * B], co
         KVC_SWITCH_B(bv, CALL);                                       \
     }
 
-template <int G, int B, int NK>
+template <int G, int B, int KM>
 __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const DevSide& V, const uint8_t* __restrict__ sm,
                                                          uint8_t* __restrict__ wl, int u, int rk, int start, int end, int k_cap_tiles,
                                                          int v_cap_tiles, float* __restrict__ out, int lane) {
     using R = RopeShape<G>;
+    constexpr int NK = k_steps(KM), ks_t = k_tail(KM);
     constexpr int LM = R::LM, W0 = k_step_words(B);
+    float m1 = -1.f;
+    asm volatile("" : "+s"(m1));
+    const uint32_t e512 = exp512();
     constexpr bool kEarly = NK * W0 <= 16;  // the next tile's K fields have registers of their own
     const float4* qry = reinterpret_cast<const float4*>(sm + R::kPt + R::kKey);
     const double* om = reinterpret_cast<const double*>(sm + R::kPt + R::kKey + R::kQry);
@@ -177,7 +190,7 @@ __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const
     const int col = lane & 15, grp = lane >> 4;
     const int rv = uni(V.r[u]), bv = uni(V.b[u]), hv = bv == 8 ? 0 : (1 << (bv - 1));
     const bool nv4 = rv <= 64 && bv <= 4;
-    const int g16 = rk >> 4, rho = rk & 15, ks_t = rho ? (g16 >> 2) : 2;
+    const int g16 = rk >> 4, rho = rk & 15;
     const int ktb = 8 * rk * B, vtb = 8 * rv * bv;
     const int tile0 = start / kTile, tile_last = (end - 1) / kTile;
     const uint8_t* kstream = uni(K.codes + K.code_off[u]);
@@ -244,10 +257,7 @@ __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const
             sincospif(2.f * (float)(t - rint(t)), &sn, &c);
             tcs[lane] = float2{c, sn};
         }
-        if (ks_t < NK) {
-            if (NK == 1 || ks_t == 0) k_write_stage<B>(kb, stage, lane);
-            else k_write_stage<B>(kb + (NK - 1) * W0, stage, lane);
-        }
+        if constexpr (ks_t < 2) k_write_stage<B>(kb + ks_t * W0, stage, lane);
         wave_lds_sync();
         // R_-(t0 + st) q' as fp16 hi + lo operands (rows 4 h + st)
         rc_h8 ah[LM][4], al[LM][4];
@@ -262,13 +272,13 @@ __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const
                 const float qa[4] = {qa4.x, qa4.y, qa4.z, qa4.w}, qb[4] = {qb4.x, qb4.y, qb4.z, qb4.w};
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    split_h(fmaf(qa[v], tc[v], qb[v] * ts[v]), ah[lm][rb >> 1], al[lm][rb >> 1], 4 * (rb & 1) + v);
-                    split_h(fmaf(qb[v], tc[v], -qa[v] * ts[v]), ah[lm][2 + (rb >> 1)], al[lm][2 + (rb >> 1)], 4 * (rb & 1) + v);
+                    split_h(fmaf(qa[v], tc[v], qb[v] * ts[v]), m1, ah[lm][rb >> 1], al[lm][rb >> 1], 4 * (rb & 1) + v);
+                    split_h(fmaf(qb[v], tc[v], -qa[v] * ts[v]), m1, ah[lm][2 + (rb >> 1)], al[lm][2 + (rb >> 1)], 4 * (rb & 1) + v);
                 }
             }
         }
         float s[LM][4];
-        rope_logits<G, B, NK>(kb, stage, ks_t, XB, XS, ah, al, qs, mb, s, lane);
+        rope_logits<G, B, KM>(kb, stage, XB, XS, ah, al, m1, e512, qs, mb, s, lane);
         if constexpr (kEarly) {
 #pragma unroll
             for (int k = 0; k < NK * W0; ++k) kb[k] = kn[k];
@@ -319,10 +329,10 @@ __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const
     write_partial<G>(C, mrun, rv, hv, out, lane);
 }
 
-// Block (chunks blockIdx.x kWaves .., unit): one wavefront per chunk.
+// Block (chunks blockIdx.x kWaves .., unit, heads blockIdx.z G .. of the unit's Gq): one wavefront per chunk.
 template <int G>
 __global__ __launch_bounds__(64 * RopeShape<G>::kWaves) __attribute__((amdgpu_waves_per_eu(RopeShape<G>::W, RopeShape<G>::W)))
-void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, const int32_t* __restrict__ seq_len, int max_seq,
+void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, int Gq, const int32_t* __restrict__ seq_len, int max_seq,
                         int chunk, int n_chunks, int k_cap_tiles, int v_cap_tiles, double log2_base, int wave_lds,
                         float* __restrict__ part) {
     using R = RopeShape<G>;
@@ -357,7 +367,7 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, co
         for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const uint16_t* qh = q + ((int64_t)u * G + (hd < G ? hd : 0)) * kD + 16 * rb + 4 * grp + v;
+                const uint16_t* qh = q + ((int64_t)u * Gq + G * blockIdx.z + (hd < G ? hd : 0)) * kD + 16 * rb + 4 * grp + v;
                 a[rb][v] = hd < G ? h2f(qh[0]) : 0.f;
                 b[rb][v] = hd < G ? h2f(qh[64]) : 0.f;
                 m = fmaxf(m, fmaxf(fabsf(a[rb][v]), fabsf(b[rb][v])));
@@ -391,31 +401,31 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, co
     int Tn = uni(seq_len[u]);
     Tn = Tn < 0 ? 0 : (Tn > max_seq ? max_seq : Tn);
     const int start = uni(c * chunk), end = uni(min(Tn, start + chunk));
-    float* __restrict__ out = part + ((int64_t)u * n_chunks + c) * G * kPartStride;
+    float* __restrict__ out = part + (((int64_t)u * n_chunks + c) * Gq + G * blockIdx.z) * kPartStride;
     if (start >= end) {
         if (lane < G) { out[lane * kPartStride] = -INFINITY; out[lane * kPartStride + 1] = 0.f; }
         return;
     }
     uint8_t* wl = sm + R::kShared + wv * wave_lds;
-    if (rk > 64) {
-        KVC_SWITCH_B(bk, (rope_item<G, B_, 2>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane)));
-    } else {
-        KVC_SWITCH_B(bk, (rope_item<G, B_, 1>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane)));
+    switch (k_mode(rk)) {
+        case 0: KVC_SWITCH_B(bk, (rope_item<G, B_, 0>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane))); break;
+        case 1: KVC_SWITCH_B(bk, (rope_item<G, B_, 1>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane))); break;
+        case 2: KVC_SWITCH_B(bk, (rope_item<G, B_, 2>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane))); break;
+        default: KVC_SWITCH_B(bk, (rope_item<G, B_, 3>(K, V, sm, wl, u, rk, start, end, k_cap_tiles, v_cap_tiles, out, lane))); break;
     }
 }
 
 #ifndef KVC_ROPE_UNIT
-extern template __global__ void decode_rope_kernel<4>(DevSide, DevSide, const uint16_t*, const int32_t*, int, int, int, int, int,
-                                                      double, int, float*);
-extern template __global__ void decode_rope_kernel<8>(DevSide, DevSide, const uint16_t*, const int32_t*, int, int, int, int, int,
-                                                      double, int, float*);
-extern template __global__ void decode_rope_kernel<16>(DevSide, DevSide, const uint16_t*, const int32_t*, int, int, int, int, int,
-                                                       double, int, float*);
+extern template __global__ void decode_rope_kernel<4>(DevSide, DevSide, const uint16_t*, int, const int32_t*, int, int, int, int,
+                                                      int, double, int, float*);
+extern template __global__ void decode_rope_kernel<8>(DevSide, DevSide, const uint16_t*, int, const int32_t*, int, int, int, int,
+                                                      int, double, int, float*);
 
 namespace {
 
+// Gq query heads per unit, G of them per item.
 template <int G>
-int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, const int32_t* seq_len, int32_t max_seq_len,
+int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, int Gq, const int32_t* seq_len, int32_t max_seq_len,
                   double log2_base, int stage_bytes, float* part, int* n_chunks, hipStream_t st) {
     using R = RopeShape<G>;
     const int U = k->n_units, tpu = (max_seq_len + kTile - 1) / kTile;
@@ -434,13 +444,13 @@ int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
     for (int n = 1; n <= *n_chunks; ++n) {
         const int c = (tpu + n - 1) / n;
         if ((tpu + c - 1) / c != n || c > kMaxChunkTiles) continue;
-        const int64_t items = (int64_t)U * ((n + R::kWaves - 1) / R::kWaves) * R::kWaves;
+        const int64_t items = (int64_t)U * (Gq / G) * ((n + R::kWaves - 1) / R::kWaves) * R::kWaves;
         const double cost = (double)((items + slots - 1) / slots) * (c + 2.0) + 0.1 * c;
         if (best < 0.0 || cost < best) { best = cost; best_n = n; best_c = c; }
     }
     *n_chunks = best_n;
-    hipLaunchKernelGGL(decode_rope_kernel<G>, dim3((best_n + R::kWaves - 1) / R::kWaves, U), dim3(64 * R::kWaves), smem, st, dev_side(k),
-                       dev_side(v), q, seq_len, max_seq_len, best_c * kTile, best_n, kct, vct, log2_base, wave_lds, part);
+    hipLaunchKernelGGL(decode_rope_kernel<G>, dim3((best_n + R::kWaves - 1) / R::kWaves, U, Gq / G), dim3(64 * R::kWaves), smem, st, dev_side(k),
+                       dev_side(v), q, Gq, seq_len, max_seq_len, best_c * kTile, best_n, kct, vct, log2_base, wave_lds, part);
     return check_launch("kvc_decode_attn_rope");
 }
 
@@ -449,11 +459,12 @@ int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
 int launch_rope_partials(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, int32_t G, const int32_t* seq_len,
                          int32_t max_seq_len, double log2_base, int stage_bytes, float* part, int* n_chunks, hipStream_t st) {
     switch (G) {
-        case 1: return launch_rope_g<1>(k, v, q, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
-        case 2: return launch_rope_g<2>(k, v, q, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
-        case 4: return launch_rope_g<4>(k, v, q, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
-        case 8: return launch_rope_g<8>(k, v, q, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
-        default: return launch_rope_g<16>(k, v, q, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
+        case 1: return launch_rope_g<1>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
+        case 2: return launch_rope_g<2>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
+        case 4: return launch_rope_g<4>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
+        // sixteen heads as two items of eight, which rebuild the keys twice: at 16 the accumulators and query
+        // operands take one wavefront per SIMD and spill (64 units x 16k, 2 bpd: 391 us in one, KVC_MEAS in two)
+        default: return launch_rope_g<8>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
     }
 }
 #endif  // KVC_ROPE_UNIT

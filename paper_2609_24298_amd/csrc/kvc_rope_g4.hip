@@ -5,6 +5,6 @@
 #include "kvc_rope.hip"
 
 namespace kvc {
-template __global__ void decode_rope_kernel<4>(DevSide, DevSide, const uint16_t*, const int32_t*, int, int, int, int, int, double,
-                                               int, float*);
+template __global__ void decode_rope_kernel<4>(DevSide, DevSide, const uint16_t*, int, const int32_t*, int, int, int, int, int,
+                                               double, int, float*);
 }  // namespace kvc
