@@ -11,12 +11,17 @@ typedef float rc_f4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------- operands
 
-// P^T in LDS: one row of kBtPitch halves per feature, its coordinates in the order of the operand
-// that meets it (the order of the contraction index is free):
+// P^T in LDS in fragment order: 1 KB per (16 features rb, matrix step s), 16 bytes per lane (feature
+// 16 rb + col, positions 32 s + 8 grp + [0, 8)), so that operand reads are contiguous over the wavefront
+// (padded feature rows cost 40 % of the reads' LDS cycles in bank conflicts). The 16 lanes of a lane row are
+// permuted by their low bits (slot col ^ grp), which spreads the staging writes over four bank groups. The
+// coordinates are in the order of the operand that meets them (the order of the contraction index is free):
 //  K: matrix step s, lane part kq, element e <-> coordinate 16 (4 (s / 2) + kq) + 4 (s % 2) + e / 2 + 8 (e % 2),
 //     which is where the code pairs (m, m + 8) of a token's 16-code field land (k_pairs);
 //  V: position 64 a + 4 c + n <-> coordinate 16 (4 a + n) + c, where the transposed value bytes land.
-constexpr int kBtPitch = kD + 8;
+constexpr int kBtBytes = kD * kD * 2;
+__host__ __device__ constexpr int bt_block(int rb, int s) { return (4 * rb + s) * 1024; }
+__device__ __forceinline__ int bt_lane(int col, int grp) { return 256 * grp + 16 * (col ^ grp); }
 
 template <int side>
 __host__ __device__ constexpr int bt_coord(int p) {
@@ -28,9 +33,9 @@ __host__ __device__ constexpr int bt_coord(int p) {
 }
 
 // Stages P^T (rows of P past the rank are zero, so codes past the rank meet zeros): a thread takes four
-// positions and eight features, lanes consecutive positions (conflict-free 8-byte LDS writes).
+// positions and eight features, lanes consecutive positions.
 template <int side, int THREADS>
-__device__ __forceinline__ void stage_basis_t(uint16_t* __restrict__ PT, const uint16_t* __restrict__ P, int r, int tid) {
+__device__ __forceinline__ void stage_basis_t(uint8_t* __restrict__ PT, const uint16_t* __restrict__ P, int r, int tid) {
     for (int e = tid; e < (kD / 4) * (kD / 8); e += THREADS) {
         const int w = e & (kD / 4 - 1), f0 = 8 * (e / (kD / 4));
         uint32_t x[4][4];
@@ -43,7 +48,8 @@ __device__ __forceinline__ void stage_basis_t(uint16_t* __restrict__ PT, const u
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const uint32_t sel = (k & 1) ? 0x07060302u : 0x05040100u;
-            *reinterpret_cast<uint2*>(PT + (f0 + k) * kBtPitch + 4 * w) =
+            const int f = f0 + k;
+            *reinterpret_cast<uint2*>(PT + bt_block(f >> 4, w >> 3) + bt_lane(f & 15, (w >> 1) & 3) + 8 * (w & 1)) =
                 uint2{perm(x[1][k >> 1], x[0][k >> 1], sel), perm(x[3][k >> 1], x[2][k >> 1], sel)};
         }
     }

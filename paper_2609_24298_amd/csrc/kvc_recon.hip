@@ -26,11 +26,11 @@ constexpr int kRecWaves = 4;
 constexpr int kZbPitch = kD + 4;                       // 33 dwords: the quarters' rows fall on different banks
 constexpr int kRecWaveLds = kTile * kZbPitch;          // also holds a staged K-step (at most 512 * 8 + 32 bytes)
 static_assert(kRecWaveLds >= 512 * 8 + 32, "staged K-step exceeds the wavefront's LDS");
-constexpr int kRecShared = kD * kBtPitch * 2;
+constexpr int kRecShared = kBtBytes;
 
 // The 16 columns of tokens in za and the 16 in zb times P^T, to the rows of tokens ta and tb (< 0: none).
 template <int NS>
-__device__ __forceinline__ void rec_store_pair(const uint16_t* __restrict__ PT, const rc_h8 (&za)[NS], const rc_h8 (&zb)[NS],
+__device__ __forceinline__ void rec_store_pair(const uint8_t* __restrict__ PT, const rc_h8 (&za)[NS], const rc_h8 (&zb)[NS],
                                                float step, bool vec, float* __restrict__ oa, float* __restrict__ ob,
                                                int col, int grp) {
 #pragma unroll
@@ -38,7 +38,7 @@ __device__ __forceinline__ void rec_store_pair(const uint16_t* __restrict__ PT, 
         rc_f4 ca = rc_f4{0.f, 0.f, 0.f, 0.f}, cb = ca;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const rc_h8 p = *reinterpret_cast<const rc_h8*>(PT + (16 * rb + col) * kBtPitch + 32 * s + 8 * grp);
+            const rc_h8 p = *reinterpret_cast<const rc_h8*>(PT + bt_block(rb, s) + bt_lane(col, grp));
             ca = mfma_h(p, za[s], ca);
             cb = mfma_h(p, zb[s], cb);
         }
@@ -60,7 +60,7 @@ __device__ __forceinline__ void rec_store_pair(const uint16_t* __restrict__ PT, 
 
 // K tile: NS = 2 nk matrix steps, nk K-steps of four coordinate groups.
 template <int B, int NK>
-__device__ __forceinline__ void rec_tile_k(const uint16_t* __restrict__ PT, uint8_t* __restrict__ stage,
+__device__ __forceinline__ void rec_tile_k(const uint8_t* __restrict__ PT, uint8_t* __restrict__ stage,
                                            const __amdgpu_buffer_rsrc_t rs, int r, float step, bool vec, float* __restrict__ out,
                                            int tok0, int lo, int hi, int lane) {
     const int col = lane & 15, grp = lane >> 4;
@@ -111,7 +111,7 @@ __device__ __forceinline__ void rec_tile_k(const uint16_t* __restrict__ PT, uint
 
 // V tile, NH halves of four N-tiles each (64 coordinates, two matrix steps).
 template <int B, int NH>
-__device__ __forceinline__ void rec_tile_v(const uint16_t* __restrict__ PT, uint8_t* __restrict__ zb,
+__device__ __forceinline__ void rec_tile_v(const uint8_t* __restrict__ PT, uint8_t* __restrict__ zb,
                                            const __amdgpu_buffer_rsrc_t rs, int r, float step, bool vec, float* __restrict__ out,
                                            int tok0, int lo, int hi, int lane) {
     const int col = lane & 15, grp = lane >> 4;
@@ -198,7 +198,7 @@ __device__ __forceinline__ void rec_tile_v(const uint16_t* __restrict__ PT, uint
 }
 
 template <int side, int B, int NK>
-__device__ __forceinline__ void rec_tiles(const DevSide& s, const uint16_t* __restrict__ PT, uint8_t* __restrict__ wl, int u, int r,
+__device__ __forceinline__ void rec_tiles(const DevSide& s, const uint8_t* __restrict__ PT, uint8_t* __restrict__ wl, int u, int r,
                                           int cap_tiles, int t0, int n_tok, int tile_first, int n_tiles, int tpb, bool vec,
                                           float* __restrict__ out, int wv, int lane) {
     const float step = s.delta[u];
@@ -219,7 +219,7 @@ __device__ __forceinline__ void rec_tiles(const DevSide& s, const uint16_t* __re
 template <int side>
 __global__ __launch_bounds__(64 * kRecWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void reconstruct_kernel(
     DevSide s, int cap_tiles, int t0, int n_tok, int tile_first, int n_tiles, int tpb, int vec, float* __restrict__ out) {
-    uint16_t* PT = reinterpret_cast<uint16_t*>(kvc_dsm);
+    uint8_t* PT = kvc_dsm;
     const int u = blockIdx.y, wv = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int r = uni(s.r[u]), b = uni(s.b[u]);
     stage_basis_t<side, 64 * kRecWaves>(PT, s.basis + s.basis_off[u], r, threadIdx.x);

@@ -35,11 +35,10 @@ namespace kvc {
 template <int G> struct RopeShape {
     static constexpr int LM = Shape<G>::LM;
     static constexpr int W = 2;   // wavefronts per SIMD the register budget is cut for
-    static constexpr int NB = 1;  // token blocks per read of a P_K^T operand (two spill: 3-20 % slower)
     // Wavefronts per block (they share P_K^T and the query table): two blocks of four per CU, or one of
     // eight for G = 8, whose query table does not leave room for two.
     static constexpr int kWaves = G == 8 ? 8 : 4;
-    static constexpr int kPt = kD * kBtPitch * 2;                    // P_K^T
+    static constexpr int kPt = kBtBytes;                             // P_K^T
     static constexpr int kKey = 4 * 64 * 8 * 4;                      // cos, sin of 4 col positions: [rb][2][lane] float4
     static constexpr int kQry = LM * 8 * 64 * 16;                    // R_-st q': [lm][8][lane] float4
     static constexpr int kShared = kPt + kKey + kQry + 64 * 8 + 64;  // + frequencies (fp64), per-head logit scales
@@ -67,91 +66,81 @@ __device__ __forceinline__ void rope_logits(const uint32_t (&kb)[k_steps(KM) * 2
                                             float m1, uint32_t e512, const float (&qs)[Shape<G>::LM], const float (&off)[Shape<G>::LM],
                                             float (&s)[Shape<G>::LM][4], int lane) {
     constexpr int NK = k_steps(KM), ks_t = k_tail(KM);
-    constexpr int LM = Shape<G>::LM, NB = RopeShape<G>::NB, W0 = k_step_words(B);
+    constexpr int LM = Shape<G>::LM, W0 = k_step_words(B);
     const int col = lane & 15, grp = lane >> 4;
-#pragma unroll
-    for (int sp = 0; sp < 4; sp += NB) {
-        // Opaque LDS offsets: the operands are the same for every block, and read again for each they take
+    // K^T of block st
+    auto rebuild = [&](int st, rc_f4 (&Cr)[8]) {
+        // Opaque LDS offset: the operands are the same for every block, and read again for each they take
         // no registers in between.
-        int po = (col * kBtPitch + 8 * grp) * 2, ko = RopeShape<G>::kPt + 16 * lane;
-        asm volatile("" : "+v"(po), "+v"(ko));
+        int po = bt_lane(col, grp);
+        asm volatile("" : "+v"(po));
         const uint8_t* pt = kvc_dsm + po;
-        const uint8_t* kc = kvc_dsm + ko;
-        rc_f4 Cr[NB][8];
 #pragma unroll
-        for (int h = 0; h < NB; ++h)
-#pragma unroll
-            for (int rb = 0; rb < 8; ++rb) Cr[h][rb] = rc_f4{0.f, 0.f, 0.f, 0.f};
+        for (int rb = 0; rb < 8; ++rb) Cr[rb] = rc_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < NK; ++ks) {
-            rc_h8 z[NB][2];
-#pragma unroll
-            for (int h = 0; h < NB; ++h) {
-                Fld f[3];
-                if (ks == ks_t) {
-                    k_fields_staged<B>(stage, xb + (sp + h) * xs, f);
-                    k_pairs<B>(f, false, e512, z[h]);
-                } else {
-                    k_fields_direct<B>(kb + ks * W0, sp + h, f);
-                    k_pairs<B>(f, ((sp + h) & 1) != 0, e512, z[h]);
-                }
+            rc_h8 z[2];
+            Fld f[3];
+            if (ks == ks_t) {
+                k_fields_staged<B>(stage, xb + st * xs, f);
+                k_pairs<B>(f, false, e512, z);
+            } else {
+                k_fields_direct<B>(kb + ks * W0, st, f);
+                k_pairs<B>(f, (st & 1) != 0, e512, z);
             }
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int rb = 0; rb < 8; ++rb) {
-                    const rc_h8 p = *reinterpret_cast<const rc_h8*>(pt + (16 * rb * kBtPitch + 32 * (2 * ks + m)) * 2);
-#pragma unroll
-                    for (int h = 0; h < NB; ++h) Cr[h][rb] = mfma_h(p, z[h][m], Cr[h][rb]);
-                }
+                for (int rb = 0; rb < 8; ++rb)
+                    Cr[rb] = mfma_h(*reinterpret_cast<const rc_h8*>(pt + bt_block(rb, 2 * ks + m)), z[m], Cr[rb]);
         }
-        // rotation by 4 col positions, the split, and the logits, two rotation pair groups at a time
-        // (matrix step ks takes features 32 ks + ..: pair groups rb = 2 ks, 2 ks + 1 and their partners)
+    };
+    // rotation of block st by 4 col positions, the split, and the logits, two rotation pair groups at a time
+    // (matrix step ks takes features 32 ks + ..: pair groups rb = 2 ks, 2 ks + 1 and their partners)
+    auto score = [&](int st, const rc_f4 (&Cr)[8]) {
+        int ko = RopeShape<G>::kPt + 16 * lane;
+        asm volatile("" : "+v"(ko));
+        const uint8_t* kc = kvc_dsm + ko;
         constexpr int NS = LM == 1 ? 3 : 1;  // one accumulator per product, or one in all (registers)
-        rc_f4 S[NB][LM][NS];
+        rc_f4 S[LM][NS];
 #pragma unroll
-        for (int h = 0; h < NB; ++h)
+        for (int lm = 0; lm < LM; ++lm)
 #pragma unroll
-            for (int lm = 0; lm < LM; ++lm)
-#pragma unroll
-                for (int t = 0; t < NS; ++t) S[h][lm][t] = rc_f4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < NS; ++t) S[lm][t] = rc_f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            float4 cs[2][2];
+            rc_h8 xh, xl, yh, yl;  // features below and above d / 2
 #pragma unroll
             for (int r2 = 0; r2 < 2; ++r2) {
-                cs[r2][0] = *reinterpret_cast<const float4*>(kc + ((2 * ks + r2) * 2) * 1024);
-                cs[r2][1] = *reinterpret_cast<const float4*>(kc + ((2 * ks + r2) * 2 + 1) * 1024);
+                const float4 c0 = *reinterpret_cast<const float4*>(kc + ((2 * ks + r2) * 2) * 1024);
+                const float4 c1 = *reinterpret_cast<const float4*>(kc + ((2 * ks + r2) * 2 + 1) * 1024);
+                const float cc[4] = {c0.x, c0.z, c1.x, c1.z}, ss[4] = {c0.y, c0.w, c1.y, c1.w};
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float a = Cr[2 * ks + r2][v], b = Cr[2 * ks + r2 + 4][v];
+                    split_h(fmaf(a, cc[v], -b * ss[v]), m1, xh, xl, 4 * r2 + v);
+                    split_h(fmaf(a, ss[v], b * cc[v]), m1, yh, yl, 4 * r2 + v);
+                }
             }
 #pragma unroll
-            for (int h = 0; h < NB; ++h) {
-                rc_h8 xh, xl, yh, yl;  // features below and above d / 2
-#pragma unroll
-                for (int r2 = 0; r2 < 2; ++r2)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const float c = (v & 1) ? cs[r2][v >> 1].z : cs[r2][v >> 1].x, sn = (v & 1) ? cs[r2][v >> 1].w : cs[r2][v >> 1].y;
-                        const float a = Cr[h][2 * ks + r2][v], b = Cr[h][2 * ks + r2 + 4][v];
-                        split_h(fmaf(a, c, -b * sn), m1, xh, xl, 4 * r2 + v);
-                        split_h(fmaf(a, sn, b * c), m1, yh, yl, 4 * r2 + v);
-                    }
-#pragma unroll
-                for (int lm = 0; lm < LM; ++lm) {
-                    S[h][lm][0] = mfma_h(ah[lm][ks], xh, S[h][lm][0]);
-                    S[h][lm][1 % NS] = mfma_h(ah[lm][ks], xl, S[h][lm][1 % NS]);
-                    S[h][lm][2 % NS] = mfma_h(al[lm][ks], xh, S[h][lm][2 % NS]);
-                    S[h][lm][0] = mfma_h(ah[lm][ks + 2], yh, S[h][lm][0]);
-                    S[h][lm][1 % NS] = mfma_h(ah[lm][ks + 2], yl, S[h][lm][1 % NS]);
-                    S[h][lm][2 % NS] = mfma_h(al[lm][ks + 2], yh, S[h][lm][2 % NS]);
-                }
+            for (int lm = 0; lm < LM; ++lm) {
+                S[lm][0] = mfma_h(ah[lm][ks], xh, S[lm][0]);
+                S[lm][1 % NS] = mfma_h(ah[lm][ks], xl, S[lm][1 % NS]);
+                S[lm][2 % NS] = mfma_h(al[lm][ks], xh, S[lm][2 % NS]);
+                S[lm][0] = mfma_h(ah[lm][ks + 2], yh, S[lm][0]);
+                S[lm][1 % NS] = mfma_h(ah[lm][ks + 2], yl, S[lm][1 % NS]);
+                S[lm][2 % NS] = mfma_h(al[lm][ks + 2], yh, S[lm][2 % NS]);
             }
         }
 #pragma unroll
-        for (int h = 0; h < NB; ++h)
+        for (int lm = 0; lm < LM; ++lm)
+            s[lm][st] = fmaf(NS == 3 ? S[lm][0][st] + (S[lm][1 % NS][st] + S[lm][2 % NS][st]) : S[lm][0][st], qs[lm], off[lm]);
+    };
 #pragma unroll
-            for (int lm = 0; lm < LM; ++lm)
-                s[lm][sp + h] = fmaf(NS == 3 ? S[h][lm][0][sp + h] + (S[h][lm][1 % NS][sp + h] + S[h][lm][2 % NS][sp + h]) : S[h][lm][0][sp + h],
-                                     qs[lm], off[lm]);
+    for (int st = 0; st < 4; ++st) {
+        rc_f4 Cr[8];
+        rebuild(st, Cr);
+        score(st, Cr);
     }
 }
 
@@ -345,7 +334,7 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, in
     double* om = reinterpret_cast<double*>(sm + R::kPt + R::kKey + R::kQry);
     float* qsc = reinterpret_cast<float*>(sm + R::kPt + R::kKey + R::kQry + 64 * 8);
     if (tid < 64) om[tid] = exp2(-(double)tid / 64.0 * log2_base) * 0.15915494309189535;  // turns per position of pair tid
-    stage_basis_t<KVC_SIDE_K, T>(reinterpret_cast<uint16_t*>(sm), K.basis + K.basis_off[u], rk, tid);
+    stage_basis_t<KVC_SIDE_K, T>(sm, K.basis + K.basis_off[u], rk, tid);
     __syncthreads();
     // cos, sin of n positions of pair j (turns reduced in fp64)
     auto turn = [&](int n, int j, float& c, float& sn) {
@@ -463,7 +452,7 @@ int launch_rope_partials(const kvc_stream_desc* k, const kvc_stream_desc* v, con
         case 2: return launch_rope_g<2>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
         case 4: return launch_rope_g<4>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
         // sixteen heads as two items of eight, which rebuild the keys twice: at 16 the accumulators and query
-        // operands take one wavefront per SIMD and spill (64 units x 16k, 2 bpd: 391 us in one, KVC_MEAS in two)
+        // operands take one wavefront per SIMD and spill (64 units x 16k, 2 bpd: 391 us in one, 199 us in two)
         default: return launch_rope_g<8>(k, v, q, G, seq_len, max_seq_len, log2_base, stage_bytes, part, n_chunks, st);
     }
 }
