@@ -1107,167 +1107,157 @@ extern template __global__ void decode_partial_kernel<8>(DevSide, DevSide, const
                                                          int, int, int, int, float*);
 #endif
 
+#ifndef KVC_DECODE_PARTIALS_UNIT
 // ---------------------------------------------------------------- combine
 
-// One block of WC wavefronts per unit (one for a few chunks, more when the context is split into
-// many). Lane l handles rank coordinates l and l + 64 of the merge and output columns 2 l, 2 l + 1.
-// The chunks' partials merge in the log2 domain (M = max m_c, L = sum l_c 2^(m_c - M),
-// A_j = sum acc_c,j 2^(m_c - M)): wavefront w merges chunks w, w + WC, ... (a batch of chunks in
-// flight at once, the running sums rescaled when a batch raises M), the wavefronts' merges meet in
-// LDS, and z_j = step_V (A_j / L + 1/2) is the dequantised rank-space average. Then o = P_V^T z (the
-// V reconstruction of Lemma lem:head-dist applied after the softmax average, which is linear), with
-// the heads shared among the wavefronts (G / WC each, at least one), each loading its two columns
-// of every basis row at the start.
-constexpr int kCombMaxRed = 32;  // WC x G at most (LDS of the cross-wavefront merge)
-template <int G, int WC>
-__global__ __launch_bounds__(64 * WC) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void combine_kernel(DevSide V, int n_chunks, const float* __restrict__ part, float* __restrict__ out) {
-    static_assert(WC * G <= kCombMaxRed || WC == 1, "combine_kernel: cross-wavefront merge exceeds its LDS");
-    constexpr int Wc = WC;
-    constexpr int GH = G / WC > 0 ? G / WC : 1;          // heads whose output one wavefront computes
-    constexpr int kCombBatch = 16 / G > 0 ? 16 / G : 1;  // chunks whose partials are in flight together (per wavefront)
-    __shared__ float zs[G][kD];
-    extern __shared__ float comb_dsm[];  // [WC * G][kPartStride] per (wavefront, head): M, L, -, -, A[128]
-    const int u = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int gb = wv * GH;  // first head of this wavefront's output (none when gb >= G)
-    float(*red)[kPartStride] = reinterpret_cast<float(*)[kPartStride]>(comb_dsm);
+// One block of four wavefronts per (unit, GB query heads). The chunks' partials merge in the log2 domain
+// (M = max m_c, L = sum l_c 2^(m_c - M), A_j = sum acc_c,j 2^(m_c - M)), z_j = step_V (A_j / L + 1/2) is the
+// dequantised rank-space average, and o = P_V^T z (the V reconstruction of Lemma lem:head-dist applied after
+// the softmax average, which is linear).
+//
+// The kernel is a chain of latencies, not of bandwidth, so that its loads leave together: a lane takes a
+// chunk's (m, l), a thread four coordinates of every (8 / GB)-th chunk of one head (up to eight in flight
+// before the weights are known) and four columns of every eighth basis row. With one block per unit that
+// merged its chunks serially (a wavefront's chunks one batch after another) the combine took more than the
+// partials of a short context: 14.5 us after partials of 6.2 us (8 units x 4k, G = 4), now 5.5; 64 units x 32k
+// 11.7 and 5.4, 256 units x 128k 12.2 and 7.4, 640 units, G = 8, 26 and 18.
+constexpr int kCombThreads = 256;
+constexpr int kCombRows = kCombThreads / 32;  // rows of 32 threads
+// Chunks merged at a time (their weights are in LDS).
+__host__ __device__ constexpr int comb_chunks(int gb) { return gb <= 2 ? 512 : 256; }
+constexpr int kCombMaxHeads = 8;              // heads per block at most
+constexpr int kCombBlocksPerCu = 2;           // blocks at which heads start to share one
+template <int GB>
+__global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(GB <= 2 ? 2 : 4)))
+void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ part,
+                                                               float* __restrict__ out) {
+    static_assert(kCombRows % GB == 0, "a head takes whole rows of threads");
+    constexpr int CS = kCombRows / GB, PF = GB <= 2 ? 8 : 4, RP = kD / kCombRows, NW = kCombThreads / 64, NB = comb_chunks(GB), ML = NB / 64;
+    __shared__ float wt[GB][NB];                                   // 2^(m_c - M)
+    __shared__ float run[3][GB];                                   // M, L, the batch's rescale
+    __shared__ __attribute__((aligned(16))) float red[kCombRows][kD];
+    __shared__ float zs[GB][kD];
+    __shared__ __attribute__((aligned(16))) float os[NW][GB][kD];
+    const int u = blockIdx.x, h0 = blockIdx.y * GB, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int q4 = tid & 31, row = tid >> 5, hr = row % GB, cr = row / GB;
+    const float* __restrict__ pu = part + ((int64_t)u * n_chunks * G + h0) * kPartStride;
+    const int64_t cstride = (int64_t)G * kPartStride;
     const int rv = V.r[u];
-    const float step = V.delta[u];
-    // the lane's two columns of every basis row, in flight while the chunks merge
-    const uint32_t* __restrict__ P32 = reinterpret_cast<const uint32_t*>(V.basis + V.basis_off[u]);
-    uint32_t pw[kD];
+    const uint2* __restrict__ P2 = reinterpret_cast<const uint2*>(V.basis + V.basis_off[u]) + q4;
+    uint2 pw[RP];
+    float4 A = float4{0.f, 0.f, 0.f, 0.f}, pre[PF];
+    // coordinates 4 q4 .. of chunks c0 + cr + k CS of the batch of nb chunks at b0
+    auto load_acc = [&](int b0, int nb, int c0) {
+        const float* __restrict__ pa = pu + b0 * cstride + hr * kPartStride + 4 + 4 * q4;
 #pragma unroll
-    for (int i = 0; i < kD; ++i) pw[i] = (gb < G && i < rv) ? P32[i * (kD / 2) + lane] : 0u;
-    const float* __restrict__ pu = part + (int64_t)u * n_chunks * G * kPartStride;
-    float M[G], L[G], A0[G], A1[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) { M[g] = -INFINITY; L[g] = A0[g] = A1[g] = 0.f; }
-    for (int c0 = wv; c0 < n_chunks; c0 += kCombBatch * Wc) {
-        float mc[kCombBatch][G], lc[kCombBatch][G], a0[kCombBatch][G], a1[kCombBatch][G];
-#pragma unroll
-        for (int k = 0; k < kCombBatch; ++k) {
-            const int ck = c0 + k * Wc;
-            const int c = min(ck, n_chunks - 1);
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float* pc = pu + ((int64_t)c * G + g) * kPartStride;
-                mc[k][g] = pc[0];
-                lc[k][g] = ck < n_chunks ? pc[1] : 0.f;
-                a0[k][g] = pc[4 + lane];
-                a1[k][g] = pc[4 + 64 + lane];
-            }
+        for (int k = 0; k < PF; ++k) {
+            const int c = c0 + cr + k * CS;
+            if (c < nb) pre[k] = *reinterpret_cast<const float4*>(pa + c * cstride);
         }
+    };
+    load_acc(0, min(NB, n_chunks), 0);
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            float mb = M[g];
+    for (int k = 0; k < RP; ++k) {
+        const int i = row + kCombRows * k;
+        pw[k] = i < rv ? P2[i * (kD / 4)] : uint2{0u, 0u};
+    }
+    for (int b0 = 0; b0 < n_chunks; b0 += NB) {
+        const int nb = min(NB, n_chunks - b0);
+        const float* __restrict__ pb = pu + b0 * cstride;
+        if (b0 > 0) {
+            __syncthreads();  // the last batch's weights have been read
+            load_acc(b0, nb, 0);
+        }
+        for (int g = wv; g < GB; g += NW) {
+            float2 ml[ML];
+            const float Mo = b0 == 0 ? -INFINITY : run[0][g], Lo = b0 == 0 ? 0.f : run[1][g];
+            float M = Mo;
 #pragma unroll
-            for (int k = 0; k < kCombBatch; ++k)
-                if (lc[k][g] > 0.f) mb = fmaxf(mb, mc[k][g]);
-            if (mb > M[g]) {  // M[g] = -inf before the first non-empty chunk: the sums are still zero
-                const float sc = M[g] == -INFINITY ? 0.f : exp2f(M[g] - mb);
-                L[g] *= sc; A0[g] *= sc; A1[g] *= sc;
-                M[g] = mb;
-            }
-#pragma unroll
-            for (int k = 0; k < kCombBatch; ++k) {
-                if (lc[k][g] > 0.f) {  // an empty chunk (or a batch slot past the last) has l = 0 and no accumulator
-                    const float w = exp2f(mc[k][g] - M[g]);
-                    L[g] = fmaf(lc[k][g], w, L[g]);
-                    A0[g] = fmaf(a0[k][g], w, A0[g]);
-                    A1[g] = fmaf(a1[k][g], w, A1[g]);
+            for (int k = 0; k < ML; ++k) {
+                if (64 * k < nb) {
+                    const int c = 64 * k + lane;
+                    ml[k] = c < nb ? *reinterpret_cast<const float2*>(pb + c * cstride + g * kPartStride) : float2{-INFINITY, 0.f};
+                    if (ml[k].y > 0.f) M = fmaxf(M, ml[k].x);  // an empty chunk has l = 0 and no accumulator
                 }
             }
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) M = fmaxf(M, __shfl_xor(M, m));
+            float L = 0.f;
+#pragma unroll
+            for (int k = 0; k < ML; ++k) {
+                if (64 * k < nb) {
+                    const float w = ml[k].y > 0.f ? exp2f(ml[k].x - M) : 0.f;
+                    wt[g][64 * k + lane] = w;
+                    if (ml[k].y > 0.f) L = fmaf(ml[k].y, w, L);
+                }
+            }
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) L += __shfl_xor(L, m);
+            const float sc = Mo == -INFINITY ? 0.f : exp2f(Mo - M);
+            if (lane == 0) {
+                run[0][g] = M;
+                run[1][g] = fmaf(Lo, sc, L);
+                run[2][g] = sc;
+            }
+        }
+        __syncthreads();
+        if (b0 > 0) {
+            const float sc = run[2][hr];
+            A.x *= sc; A.y *= sc; A.z *= sc; A.w *= sc;
+        }
+        for (int c0 = 0; c0 < nb; c0 += PF * CS) {
+            if (c0 > 0) load_acc(b0, nb, c0);
+#pragma unroll
+            for (int k = 0; k < PF; ++k) {
+                const int c = c0 + cr + k * CS;
+                const float w = c < nb ? wt[hr][c] : 0.f;
+                const bool on = w != 0.f;  // an empty chunk's accumulator is not written
+                A.x = fmaf(on ? pre[k].x : 0.f, w, A.x);
+                A.y = fmaf(on ? pre[k].y : 0.f, w, A.y);
+                A.z = fmaf(on ? pre[k].z : 0.f, w, A.z);
+                A.w = fmaf(on ? pre[k].w : 0.f, w, A.w);
+            }
         }
     }
+    *reinterpret_cast<float4*>(&red[row][4 * q4]) = A;
+    __syncthreads();
+    const float step = V.delta[u];
+    for (int e = tid; e < GB * kD; e += kCombThreads) {
+        const int g = e / kD, j = e % kD;
+        const float L = run[1][g];
+        float a = 0.f;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        float* rd = red[wv * G + g];
-        if (lane == 0) { rd[0] = M[g]; rd[1] = L[g]; }
-        rd[4 + lane] = A0[g];
-        rd[4 + 64 + lane] = A1[g];
+        for (int c = 0; c < CS; ++c) a += red[c * GB + g][j];
+        zs[g][j] = (L > 0.f && j < rv) ? step * fmaf(a, 1.f / L, 0.5f) : 0.f;
     }
     __syncthreads();
-    for (int g = wv; g < G; g += Wc) {  // the wavefronts' merges of head g, then z
-        float Mg = -INFINITY;
-        for (int w = 0; w < Wc; ++w)
-            if (red[w * G + g][1] > 0.f) Mg = fmaxf(Mg, red[w * G + g][0]);
-        float Lg = 0.f, B0 = 0.f, B1 = 0.f;
-        for (int w = 0; w < Wc; ++w) {
-            const float* rd = red[w * G + g];
-            if (rd[1] > 0.f) {
-                const float sc = exp2f(rd[0] - Mg);
-                Lg = fmaf(rd[1], sc, Lg);
-                B0 = fmaf(rd[4 + lane], sc, B0);
-                B1 = fmaf(rd[4 + 64 + lane], sc, B1);
-            }
+    // the basis words stay packed until here
+#pragma unroll
+    for (int k = 0; k < RP; ++k) asm volatile("" : "+v"(pw[k].x), "+v"(pw[k].y));
+#pragma unroll
+    for (int g = 0; g < GB; ++g) {
+        float4 o = float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < RP; ++k) {
+            const float z = zs[g][row + kCombRows * k];  // zero past the rank
+            o.x = fmaf(h2f((uint16_t)(pw[k].x & 0xffffu)), z, o.x);
+            o.y = fmaf(h2f((uint16_t)(pw[k].x >> 16)), z, o.y);
+            o.z = fmaf(h2f((uint16_t)(pw[k].y & 0xffffu)), z, o.z);
+            o.w = fmaf(h2f((uint16_t)(pw[k].y >> 16)), z, o.w);
         }
-        const float inv = Lg > 0.f ? 1.f / Lg : 0.f;
-        zs[g][lane] = (Lg > 0.f && lane < rv) ? step * fmaf(B0, inv, 0.5f) : 0.f;
-        zs[g][lane + 64] = (Lg > 0.f && lane + 64 < rv) ? step * fmaf(B1, inv, 0.5f) : 0.f;
+        o.x += __shfl_xor(o.x, 32);
+        o.y += __shfl_xor(o.y, 32);
+        o.z += __shfl_xor(o.z, 32);
+        o.w += __shfl_xor(o.w, 32);
+        if (lane < 32) *reinterpret_cast<float4*>(&os[wv][g][4 * q4]) = o;
     }
     __syncthreads();
-    if (gb < G) {
-        float o0[GH], o1[GH];
-#pragma unroll
-        for (int j = 0; j < GH; ++j) o0[j] = o1[j] = 0.f;
-#pragma unroll
-        for (int i = 0; i < kD; ++i) {
-            const float p0 = h2f((uint16_t)(pw[i] & 0xffffu)), p1 = h2f((uint16_t)(pw[i] >> 16));
-#pragma unroll
-            for (int j = 0; j < GH; ++j) {
-                const float z = zs[gb + j][i];  // zero past the rank
-                o0[j] = fmaf(p0, z, o0[j]);
-                o1[j] = fmaf(p1, z, o1[j]);
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < GH; ++j)
-            reinterpret_cast<float2*>(out + ((int64_t)u * G + gb + j) * kD)[lane] = float2{o0[j], o1[j]};
+    for (int e = tid; e < GB * kD; e += kCombThreads) {
+        const int g = e / kD, j = e % kD;
+        out[((int64_t)u * G + h0) * kD + e] = (os[0][g][j] + os[1][g][j]) + (os[2][g][j] + os[3][g][j]);
     }
 }
 
-// Wavefronts of a combine block (1, 2, 4 or 8): enough that each merges about 8 chunks, within the
-// LDS of the cross-wavefront merge, and few enough that every block is resident at once (the
-// kernel's register budget leaves two wavefronts per SIMD, eight per CU).
-inline int combine_waves(int G, int n_chunks, int U, int ncu) {
-    const int cap = std::min(std::min(std::max(kCombMaxRed / G, 1), 8), std::max(1, 8 * ncu / std::max(U, 1)));
-    int w = 1;
-    while (2 * w <= cap && 8 * w < n_chunks) w *= 2;
-    return w;
-}
-
-// ---------------------------------------------------------------- host side
-
-// Combine launch with cw (a power of two that combine_waves chose for this G) wavefronts per block.
-template <int G>
-void launch_combine_g(int cw, dim3 grid, dim3 blk, size_t smem, hipStream_t st, const DevSide& V, int n_chunks,
-                    const float* part, float* out) {
-    switch (cw) {
-        case 8:
-            if constexpr (8 * G <= kCombMaxRed) {
-                hipLaunchKernelGGL((combine_kernel<G, 8>), grid, blk, smem, st, V, n_chunks, part, out);
-                return;
-            }
-            break;
-        case 4:
-            if constexpr (4 * G <= kCombMaxRed) {
-                hipLaunchKernelGGL((combine_kernel<G, 4>), grid, blk, smem, st, V, n_chunks, part, out);
-                return;
-            }
-            break;
-        case 2:
-            if constexpr (2 * G <= kCombMaxRed) {
-                hipLaunchKernelGGL((combine_kernel<G, 2>), grid, blk, smem, st, V, n_chunks, part, out);
-                return;
-            }
-            break;
-        default:
-            break;
-    }
-    hipLaunchKernelGGL((combine_kernel<G, 1>), grid, dim3(64), (size_t)G * kPartStride * 4, st, V, n_chunks, part, out);
-}
-
-#ifndef KVC_DECODE_PARTIALS_UNIT
 // ---------------------------------------------------------------- read probe
 
 // Streaming read of n16 16-byte words (non-temporal loads, grid-stride). The words fold into one
@@ -1416,17 +1406,18 @@ extern "C" size_t kvc_decode_attn_workspace(const kvc_stream_desc* k, const kvc_
 namespace kvc {
 namespace {
 
-// Combine launch for U units of n_chunks partials each.
+// Combine launch for U units of n_chunks partials each. Heads share a block, and so its basis reads, once one
+// head per block makes more blocks than are resident (two per CU at the registers of one or two heads):
+// 256 units, G = 4, 12.1 us with a head per block and 7.4 with two.
 void launch_combine(int G, int U, const DevSide& V, int n_chunks, const float* part, float* out, hipStream_t st) {
-    const int cw = combine_waves(G, n_chunks, U, device_cus());
-    const dim3 cblk(64 * cw);
-    const size_t csm = (size_t)cw * G * kPartStride * 4;
-    switch (G) {
-        case 1: launch_combine_g<1>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
-        case 2: launch_combine_g<2>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
-        case 4: launch_combine_g<4>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
-        case 8: launch_combine_g<8>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
-        default: launch_combine_g<16>(cw, dim3(U), cblk, csm, st, V, n_chunks, part, out); break;
+    int gb = 1;
+    while (gb < G && gb < kCombMaxHeads && (int64_t)U * G > (int64_t)kCombBlocksPerCu * device_cus() * gb) gb *= 2;
+    const dim3 grid(U, G / gb), blk(kCombThreads);
+    switch (gb) {
+        case 1: hipLaunchKernelGGL(combine_kernel<1>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        case 2: hipLaunchKernelGGL(combine_kernel<2>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        case 4: hipLaunchKernelGGL(combine_kernel<4>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        default: hipLaunchKernelGGL(combine_kernel<8>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
     }
 }
 
