@@ -707,7 +707,7 @@ __global__ __launch_bounds__(kStepPrepThreads) __attribute__((amdgpu_waves_per_e
 template <int G> struct Shape {
     static constexpr int LM = (G + 3) / 4;  // M-tiles of 16 rows = 4 heads x 4 limb slots (logits and PV)
     // Wavefronts per SIMD the register budget is cut for (512 / W registers per lane, no spills).
-    static constexpr int W = G <= 4 ? 3 : (G == 8 ? 2 : 1);
+    static constexpr int W = G <= 4 ? 3 : 2;
 };
 
 // Runs a KVC_SWITCH_B-style CALL with B_ = the compile-time width BKc (BVc), or switches on the
@@ -847,8 +847,8 @@ __device__ __forceinline__ void write_partial(const v4i (&C)[Shape<G>::LM][9], c
 // Inlined into the kernel: each instantiation is a disjoint branch of the dispatch, so registers
 // are allocated per branch, and no call frame saves registers to scratch memory on every item.
 template <int G, int BKc, int BVc, int KM, int NVc>
-__device__ __attribute__((always_inline)) void run_item(const DevSide& K, const DevSide& V, const v4i* __restrict__ qa_ws,
-                                         const float4* __restrict__ qk_ws, int k_cap_tiles, int v_cap_tiles, int u,
+__device__ __attribute__((always_inline)) void run_item(const DevSide& K, const DevSide& V, const v4i* __restrict__ qa_u, int ks_stride,
+                                         const float4* __restrict__ qk_u, int k_cap_tiles, int v_cap_tiles, int u,
                                          int start, int end, float* __restrict__ out, int lane) {
     constexpr int LM = Shape<G>::LM;
     constexpr int kDepth = KM >= 0 ? kPrefetchDepth : 1;
@@ -902,12 +902,12 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int lm = 0; lm < LM; ++lm) qa[ks][lm] = qa_ws[(((int64_t)u * 2 + ks) * LM + lm) * 64 + lane];
+        for (int lm = 0; lm < LM; ++lm) qa[ks][lm] = qa_u[ks * ks_stride + lm * 64 + lane];
     float k0[LM], k1[LM], k2[LM], bias[LM], mrun[LM], mb[LM];
 #pragma unroll
     for (int lm = 0; lm < LM; ++lm) {
         const int h = 4 * lm + grp;
-        const float4 v = h < G ? qk_ws[(int64_t)u * G + h] : float4{0.f, 0.f, 0.f, 0.f};
+        const float4 v = h < G ? qk_u[h] : float4{0.f, 0.f, 0.f, 0.f};
         k0[lm] = v.x; k1[lm] = v.y; k2[lm] = v.z; bias[lm] = v.w;
         mrun[lm] = -INFINITY;
         mb[lm] = 0.f;  // bias - mrun once the first tile has set mrun
@@ -1044,7 +1044,7 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
 // its K fields are one contiguous load, and its probability limbs are one dword per limb in LDS.
 template <int G>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Shape<G>::W, Shape<G>::W))) void decode_partial_kernel(
-    DevSide K, DevSide V, const v4i* __restrict__ qa_ws, const float4* __restrict__ qk_ws,
+    DevSide K, DevSide V, int Gq, const v4i* __restrict__ qa_ws, const float4* __restrict__ qk_ws,
     const int32_t* __restrict__ seq_len, int max_seq, int chunk, int n_chunks, int k_cap_tiles, int v_cap_tiles,
     float* __restrict__ part) {
     constexpr int LM = Shape<G>::LM;
@@ -1055,11 +1055,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Shape<G>::W,
     T = T < 0 ? 0 : (T > max_seq ? max_seq : T);
     const int start = c * chunk;
     const int end = min(T, start + chunk);
-    float* __restrict__ out = part + ((int64_t)u * n_chunks + c) * G * kPartStride;
+    // the item's heads: all of the unit's, except that sixteen are two items of eight
+    const int Gu = G == 8 ? Gq : G, h0 = G == 8 ? G * (int)blockIdx.z : 0, ks_stride = (Gu + 3) / 4 * 64;
+    float* __restrict__ out = part + (((int64_t)u * n_chunks + c) * Gu + h0) * kPartStride;
     if (start >= end) {
         if (lane < G) { out[lane * kPartStride] = -INFINITY; out[lane * kPartStride + 1] = 0.f; }
         return;
     }
+    const v4i* __restrict__ qa_u = qa_ws + (int64_t)u * 2 * ks_stride + h0 / 4 * 64;
+    const float4* __restrict__ qk_u = qk_ws + (int64_t)u * Gu + h0;
     const int bk = K.b[u], bv = V.b[u];
     // Compiled per (b_K, b_V, K-step structure) for value widths up to 4 and the common group sizes;
     // the general path switches on the widths per tile.
@@ -1072,7 +1076,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Shape<G>::W,
             switch ((((bk - 1) * 4 + (bv - 1)) * 4 + k_mode(K.r[u])) * 3 + nvc) {
 #define KVC_ITEM(BK, BV, KM, NV)                                                                                  \
     case (((BK - 1) * 4 + (BV - 1)) * 4 + KM) * 3 + (NV == 6 ? 1 : (NV == 4 ? 2 : 0)):                          \
-        run_item<G, BK, BV, KM, NV>(K, V, qa_ws, qk_ws, k_cap_tiles, v_cap_tiles, u, start, end, out, lane);    \
+        run_item<G, BK, BV, KM, NV>(K, V, qa_u, ks_stride, qk_u, k_cap_tiles, v_cap_tiles, u, start, end, out, lane);    \
         return;
 #define KVC_ITEM4(BK, BV) KVC_ITEM(BK, BV, 0, 8) KVC_ITEM(BK, BV, 1, 8) KVC_ITEM(BK, BV, 2, 8) KVC_ITEM(BK, BV, 3, 8)
 #define KVC_ITEM4N(BK, BV, NV) KVC_ITEM(BK, BV, 0, NV) KVC_ITEM(BK, BV, 1, NV) KVC_ITEM(BK, BV, 2, NV) KVC_ITEM(BK, BV, 3, NV)
@@ -1095,15 +1099,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Shape<G>::W,
             }
         }
     }
-    run_item<G, 0, 0, -1, 8>(K, V, qa_ws, qk_ws, k_cap_tiles, v_cap_tiles, u, start, end, out, lane);
+    run_item<G, 0, 0, -1, 8>(K, V, qa_u, ks_stride, qk_u, k_cap_tiles, v_cap_tiles, u, start, end, out, lane);
 }
 
 // The instantiations for 4 and 8 query heads per KV head are compiled in translation units of their
 // own (kvc_decode_g4.hip, kvc_decode_g8.hip), in parallel with this one.
 #ifndef KVC_DECODE_PARTIALS_UNIT
-extern template __global__ void decode_partial_kernel<4>(DevSide, DevSide, const v4i*, const float4*, const int32_t*, int,
+extern template __global__ void decode_partial_kernel<4>(DevSide, DevSide, int, const v4i*, const float4*, const int32_t*, int,
                                                          int, int, int, int, float*);
-extern template __global__ void decode_partial_kernel<8>(DevSide, DevSide, const v4i*, const float4*, const int32_t*, int,
+extern template __global__ void decode_partial_kernel<8>(DevSide, DevSide, int, const v4i*, const float4*, const int32_t*, int,
                                                          int, int, int, int, float*);
 #endif
 
@@ -1282,8 +1286,13 @@ int stage_lds_bytes(const kvc_stream_desc* k) {
     return m == 0 ? 0 : m + 32;  // funnel reads may look one word past a plane's region
 }
 
+// Query heads of one item. Sixteen are two items of eight, which read the codes twice: in one item they take
+// one wavefront per SIMD, spill and have no compiled widths (160 units x 16k, 2 bpd: 292 us in one item,
+// 84 us in two; 1 bpd 246 and 74, 4 bpd 301 and 130).
+int item_heads(int G) { return std::min(G, 8); }
+
 size_t partial_smem(int G, int stage_bytes_) {
-    const int LM = (G + 3) / 4;
+    const int LM = (item_heads(G) + 3) / 4;
     return (size_t)16 * LM * kPRowBytes + (size_t)stage_bytes_;
 }
 
@@ -1305,8 +1314,7 @@ int64_t resident_slots(int G, size_t smem) {
         case 1: nb = resident_blocks<1>(smem); break;
         case 2: nb = resident_blocks<2>(smem); break;
         case 4: nb = resident_blocks<4>(smem); break;
-        case 8: nb = resident_blocks<8>(smem); break;
-        default: nb = resident_blocks<16>(smem); break;
+        default: nb = resident_blocks<8>(smem); break;
     }
     return (int64_t)ncu * nb;
 }
@@ -1332,7 +1340,7 @@ WsLayout ws_layout(const kvc_stream_desc* k, int G, int max_seq) {
     const int U = k->n_units;
     const int LM = (G + 3) / 4;
     L.stage_bytes = stage_lds_bytes(k);
-    const int64_t slots = resident_slots(G, partial_smem(G, L.stage_bytes));
+    const int64_t slots = resident_slots(item_heads(G), partial_smem(G, L.stage_bytes));
     const int tpu = (max_seq + kTile - 1) / kTile;
     double best_cost = -1.0;
     L.chunk = std::min(tpu, kMaxChunkTiles) * kTile;
@@ -1340,7 +1348,7 @@ WsLayout ws_layout(const kvc_stream_desc* k, int G, int max_seq) {
     for (int n = 1; n <= tpu && n <= 4096; ++n) {
         const int c = (tpu + n - 1) / n;
         if ((tpu + c - 1) / c != n || c > kMaxChunkTiles) continue;
-        const int64_t items = (int64_t)U * n;
+        const int64_t items = (int64_t)U * (G / item_heads(G)) * n;
         const int64_t rounds = (items + slots - 1) / slots;
         const double cost = (double)rounds * (c + kItemOverheadTiles) + kStragglerShare * c;
         if (best_cost < 0.0 || cost < best_cost) {
@@ -1377,7 +1385,7 @@ int decode_check(const kvc_stream_desc* k, const kvc_stream_desc* v, int32_t G, 
 }
 
 template <int G>
-int launch_partials(dim3 grid, hipStream_t st, const DevSide& K, const DevSide& V, const v4i* qa, const float4* qk,
+int launch_partials(dim3 grid, int Gq, hipStream_t st, const DevSide& K, const DevSide& V, const v4i* qa, const float4* qk,
                     const int32_t* seq_len, int max_seq, int chunk, int n_chunks, int kct, int vct, float* part,
                     int stage_bytes_) {
     const size_t smem = partial_smem(G, stage_bytes_);
@@ -1386,7 +1394,7 @@ int launch_partials(dim3 grid, hipStream_t st, const DevSide& K, const DevSide& 
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return set_error(KVC_EDEVICE, "hipFuncSetAttribute: %s", hipGetErrorString(e));
     }
-    hipLaunchKernelGGL(decode_partial_kernel<G>, grid, dim3(64), smem, st, K, V, qa, qk, seq_len, max_seq, chunk,
+    hipLaunchKernelGGL(decode_partial_kernel<G>, grid, dim3(64), smem, st, K, V, Gq, qa, qk, seq_len, max_seq, chunk,
                        n_chunks, kct, vct, part);
     return KVC_OK;
 }
@@ -1453,14 +1461,13 @@ int decode_launch(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
     else
         hipLaunchKernelGGL(qprep_kernel<8>, dim3(U), dim3(512), qsm, st, K, q, G, LM, qa, qk);
     const int kct = (k->capacity + kTile - 1) / kTile, vct = (v->capacity + kTile - 1) / kTile;
-    const dim3 grid(L.n_chunks, U);
+    const dim3 grid(L.n_chunks, U, G / item_heads(G));
     int e = KVC_OK;
     switch (G) {
-        case 1: e = launch_partials<1>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
-        case 2: e = launch_partials<2>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
-        case 4: e = launch_partials<4>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
-        case 8: e = launch_partials<8>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
-        default: e = launch_partials<16>(grid, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
+        case 1: e = launch_partials<1>(grid, G, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
+        case 2: e = launch_partials<2>(grid, G, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
+        case 4: e = launch_partials<4>(grid, G, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
+        default: e = launch_partials<8>(grid, G, st, K, V, qa, qk, seq_len, max_seq_len, L.chunk, L.n_chunks, kct, vct, part, L.stage_bytes); break;
     }
     if (e) return e;
     launch_combine(G, U, V, L.n_chunks, part, out, st);

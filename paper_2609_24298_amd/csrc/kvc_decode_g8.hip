@@ -5,6 +5,6 @@
 #include "kvc_decode.hip"
 
 namespace kvc {
-template __global__ void decode_partial_kernel<8>(DevSide, DevSide, const v4i*, const float4*, const int32_t*, int, int,
+template __global__ void decode_partial_kernel<8>(DevSide, DevSide, int, const v4i*, const float4*, const int32_t*, int, int,
                                                   int, int, int, float*);
 }  // namespace kvc
