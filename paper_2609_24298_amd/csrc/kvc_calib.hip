@@ -38,12 +38,15 @@ typedef float cv_f4 __attribute__((ext_vector_type(4)));
 
 // One block per (head, 64 x 64 block of the symmetric result: both diagonal ones and the upper one), its
 // eight wavefronts taking 64-token chunks in turn. The contraction runs over tokens, so both operands
-// need 8 tokens of one feature per lane: a lane loads 8 tokens x 8 features (16-byte loads, the next
-// chunk's in flight while this one is multiplied), transposes them in registers with 32 byte permutes and
+// need 8 tokens of one feature per lane: a lane loads 8 tokens x 8 features (16-byte loads, the next two
+// chunks' in flight while one is multiplied), transposes them in registers with 32 byte permutes and
 // writes 16-byte runs of tokens to the wavefront's own LDS, from where the operands are 16-byte reads.
 // Token octets are swizzled by the feature octet, so that the writes meet no bank conflicts. The
 // wavefronts' sums meet in LDS in a fixed order; the upper block is also written transposed.
-// 40 heads x 8192 tokens: 46 us (301 us with one block per head and 2-byte gathers from LDS).
+// Bound by the latency of the loads: 40 heads make 120 blocks of eight wavefronts, all that the LDS leaves on
+// 256 CUs. 40 heads x 8192 tokens: 36 us with two chunks in flight, 46 us with one (301 us with one block
+// per head and 2-byte gathers from LDS). Buffer loads give the second chunk its registers: their bounds check
+// zeroes the rows past the last token, and the rows of a chunk share one offset.
 constexpr int kCovWaves = 8;
 constexpr int kCovThreads = 64 * kCovWaves;
 constexpr int kCovTok = 64;           // tokens per chunk
@@ -89,27 +92,22 @@ __device__ __forceinline__ void cov_accumulate(const uint16_t* __restrict__ X, i
     const int fo = lane & 7, to = lane >> 3, col = lane & 15, kq = lane >> 4;
     uint8_t* sa = sm;
     uint8_t* sb = DIAG ? sm : sm + kCovOperand;
-    uint4 wa[8], wb[8];
-    auto load = [&](int t0) {
+    constexpr int S = kCovTok * kCovWaves;
+    uint4 wa0[8], wb0[8], wa1[8], wb1[8];
+    const int va = 8 * to * (2 * kD) + 16 * fo + 2 * I0, vb = va - 2 * I0 + 2 * J0;
+    auto load = [&](int t0, uint4 (&wa)[8], uint4 (&wb)[8]) {  // rows past the last token read as zero
+        const int rows = min(max(n_tok - t0, 0), kCovTok);
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(X + (int64_t)t0 * kD), (short)0, rows * (2 * kD), 0x00020000);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const int t = t0 + 8 * to + k;
-            const uint16_t* row = X + (int64_t)(t < n_tok ? t : 0) * kD + 8 * fo;
-            const uint4 a = *reinterpret_cast<const uint4*>(row + I0);
-            wa[k] = t < n_tok ? a : uint4{0u, 0u, 0u, 0u};
-            if (!DIAG) {
-                const uint4 b = *reinterpret_cast<const uint4*>(row + J0);
-                wb[k] = t < n_tok ? b : uint4{0u, 0u, 0u, 0u};
-            }
+            wa[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, va + 2 * kD * k, 0, 0));
+            if (!DIAG) wb[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, vb + 2 * kD * k, 0, 0));
         }
     };
-    int t0 = kCovTok * wv;
-    if (t0 < n_tok) load(t0);
-    for (; t0 < n_tok; t0 += kCovTok * kCovWaves) {
+    auto chunk = [&](int t0, uint4 (&wa)[8], uint4 (&wb)[8]) {
         cov_stage(wa, sa, fo, to, fsa);
         if (!DIAG) cov_stage(wb, sb, fo, to, fsb);
-        const int tn = t0 + kCovTok * kCovWaves;
-        if (tn < n_tok) load(tn);
+        load(t0 + 2 * S, wa, wb);
         // a wavefront's LDS accesses execute in order: only the compiler's reordering has to be stopped
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -128,6 +126,13 @@ __device__ __forceinline__ void cov_accumulate(const uint16_t* __restrict__ X, i
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
+    };
+    int t0 = __builtin_amdgcn_readfirstlane(kCovTok * wv);
+    load(t0, wa0, wb0);
+    load(t0 + S, wa1, wb1);
+    for (; t0 < n_tok; t0 += 2 * S) {
+        chunk(t0, wa0, wb0);
+        if (t0 + S < n_tok) chunk(t0 + S, wa1, wb1);
     }
 }
 
