@@ -315,14 +315,17 @@ __device__ __forceinline__ void k_prefetch(uint32_t (&kb)[kKBufWords], const __a
     }
 }
 
-// Logit of token 4 col + st for the lane's heads: three int32 limb sums -> log2-domain value + off.
+// Logit of token 4 col + st for the lane's heads: three int32 limb sums (of scales k0, 254 k2, k2) -> log2-domain
+// value + off.
 template <int LM>
-__device__ __forceinline__ void logit_of(const v4i (&acc)[LM], const float (&k0)[LM], const float (&k1)[LM],
-                                         const float (&k2)[LM], const float (&off)[LM], float (&s)[LM][4], int st) {
+__device__ __forceinline__ void logit_of(const v4i (&acc)[LM], const float (&k0)[LM], const float (&k2)[LM],
+                                         const float (&off)[LM], float (&s)[LM][4], int st) {
 #pragma unroll
     for (int lm = 0; lm < LM; ++lm) {
-        float v = fmaf((float)acc[lm][2], k2[lm], off[lm]);
-        v = fmaf((float)acc[lm][1], k1[lm], v);
+        // Limbs 1 and 2 as one integer (|acc| <= 2^21, so a 24-bit multiply-add): a multiply-add and a
+        // conversion fewer per logit. Narrow codes are bound by instructions: 256 units x 128k, 0.5 bpd,
+        // 198 -> 191 us, 640 units x 64k, eight heads, 1 bpd, 438 -> 425.
+        const float v = fmaf((float)(__mul24(acc[lm][1], 254) + acc[lm][2]), k2[lm], off[lm]);
         s[lm][st] = fmaf((float)acc[lm][0], k0[lm], v);
     }
 }
@@ -337,7 +340,7 @@ __device__ __forceinline__ void k_tile(uint32_t (&kb)[kKBufWords], uint32_t (&kb
                                        const __amdgpu_buffer_rsrc_t rs_n, int rk, int nk_rt, int ks_t_rt,
                                        const uint32_t (&LK)[2], uint32_t xb, uint32_t xs, int lane,
                                        uint8_t* __restrict__ stage, const v4i (&qa)[2][LM], const float (&k0)[LM],
-                                       const float (&k1)[LM], const float (&k2)[LM], const float (&off)[LM],
+                                       const float (&k2)[LM], const float (&off)[LM],
                                        float (&s)[LM][4]) {
     constexpr int W0 = k_step_words(B);
     // K-step structure fixed at compile time when KM >= 0 (see k_mode), else taken at run time
@@ -379,7 +382,7 @@ __device__ __forceinline__ void k_tile(uint32_t (&kb)[kKBufWords], uint32_t (&kb
                     for (int lm = 0; lm < LM; ++lm) acc[lm] = mfma_i8(qa[1][lm], bk, acc[lm]);
                 }
             }
-            logit_of<LM>(acc, k0, k1, k2, off, s, st);
+            logit_of<LM>(acc, k0, k2, off, s, st);
         }
         k_load_direct<B>(rs_n, rk, LK[0], kb);
         if constexpr (kTwo) k_load_direct<B>(rs_n, rk, LK[1], kb + W0);
@@ -420,7 +423,7 @@ __device__ __forceinline__ void k_tile(uint32_t (&kb)[kKBufWords], uint32_t (&kb
             v4i acc[LM];
 #pragma unroll
             for (int lm = 0; lm < LM; ++lm) acc[lm] = S[lm][st];
-            logit_of<LM>(acc, k0, k1, k2, off, s, st);
+            logit_of<LM>(acc, k0, k2, off, s, st);
         }
     }
 }
@@ -903,12 +906,12 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int lm = 0; lm < LM; ++lm) qa[ks][lm] = qa_u[ks * ks_stride + lm * 64 + lane];
-    float k0[LM], k1[LM], k2[LM], bias[LM], mrun[LM], mb[LM];
+    float k0[LM], k2[LM], bias[LM], mrun[LM], mb[LM];
 #pragma unroll
     for (int lm = 0; lm < LM; ++lm) {
         const int h = 4 * lm + grp;
         const float4 v = h < G ? qk_u[h] : float4{0.f, 0.f, 0.f, 0.f};
-        k0[lm] = v.x; k1[lm] = v.y; k2[lm] = v.z; bias[lm] = v.w;
+        k0[lm] = v.x; k2[lm] = v.z; bias[lm] = v.w;
         mrun[lm] = -INFINITY;
         mb[lm] = 0.f;  // bias - mrun once the first tile has set mrun
     }
@@ -971,7 +974,7 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
             float off[LM];
 #pragma unroll
             for (int lm = 0; lm < LM; ++lm) off[lm] = first ? bias[lm] : mb[lm];
-            KVC_SW_K((k_tile<B_, LM, KM>(kb, kb_next, stage_next, krs, krs_n, rkt, nkt, kst, LKt, XBt, XSt, lane, stage, qa, k0, k1, k2, off, s)));
+            KVC_SW_K((k_tile<B_, LM, KM>(kb, kb_next, stage_next, krs, krs_n, rkt, nkt, kst, LKt, XBt, XSt, lane, stage, qa, k0, k2, off, s)));
         }
 
         // ---- online softmax
