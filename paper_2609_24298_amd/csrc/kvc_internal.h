@@ -22,4 +22,14 @@ inline int64_t stream_bytes(int64_t n_tok, int r, int b) {
     return ((n_tok + KVC_TILE_TOKENS - 1) / KVC_TILE_TOKENS) * 8LL * r * b;
 }
 
+// Elements of one lane of the bulk encoder that are coordinates of the unit, bit 4 nt + i for element i of
+// quarter nt, in a group of 16 coordinates of which the first `left` exist. Lane (col, grp) holds
+// coordinates 4 grp + i on the K side and coordinate col on the V side. Only these may be settled: the
+// basis has no row for the others.
+constexpr uint32_t encode_rank_mask(int side, int left, int col, int grp) {
+    if (side == KVC_SIDE_V) return col < left ? 0xffffu : 0u;
+    const int n = left - 4 * grp;
+    return n <= 0 ? 0u : (n >= 4 ? 0xffffu : 0x1111u * ((1u << n) - 1u));
+}
+
 }  // namespace kvc

@@ -366,7 +366,7 @@ __device__ __forceinline__ void encode_tiles(const uint16_t* __restrict__ Pl, co
             if (mc == n_mc - 1 && tl + kEncWaves < tl_end) load_x(tl + kEncWaves);
             // K: lane holds coordinates 16 mc + 4 grp + i of token 16 nt + col.
             // V: lane holds rows 16 nt + 4 grp + i of coordinate 16 mc + col.
-            if (mc == g16) {  // coordinates past the rank: a value that is never undecided
+            if (mc == g16) {  // coordinates past the rank: the value farthest from a threshold
 #pragma unroll
                 for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
@@ -405,6 +405,8 @@ __device__ __forceinline__ void encode_tiles(const uint16_t* __restrict__ Pl, co
                         const float tp = fmaf(acc[nt][i], inv, fh_lo);
                         if (fabsf(tp - __builtin_rintf(tp)) >= thr[nt]) ambm |= 1u << (4 * nt + i);
                     }
+                // a token long enough makes thr negative and flags even the coordinates past the rank
+                ambm &= encode_rank_mask(side, r - 16 * mc, col, grp);
                 uint64_t pend = __ballot(ambm != 0);
                 while (pend) {
                     const int L = __builtin_ctzll(pend);

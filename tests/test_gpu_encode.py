@@ -39,3 +39,29 @@ def test_bulk_pieces_bit_exact(b):
         for u, r in enumerate(RANKS):
             codes = onat.encode_codes(Ps[u], float(ds[u]), b, a[u].view(np.uint16))
             assert np.array_equal(S.unit_codes(u, T).cpu().numpy(), onat.pack(codes, r, b, side)), (side, r)
+
+
+@pytest.mark.parametrize("b", [1, 3, 8])
+def test_bulk_long_tokens_bit_exact(b):
+    # Tokens beyond 126 000 steps have an error bound above half a step, so that every element is settled; the
+    # rows after each basis are NaN bits, inside the arena.
+    rng = np.random.default_rng(90 + b)
+    ranks = (2, 14, 34, 66, 112, 126, 128)
+    n, step = 150, np.float32(0.004)
+    x = rng.standard_normal((2, len(ranks), n, 128))
+    x[:, :, ::3] *= 3000.0
+    x[:, :, 1::7] = np.sign(x[:, :, 1::7]) * 65504.0
+    x = x.astype(np.float16)
+    assert np.linalg.norm(x[:, :, ::3].astype(np.float64), axis=-1).min() > 126000 * float(step)
+    for side in (kvc.SIDE_K, kvc.SIDE_V):
+        Ps = [np.linalg.qr(rng.standard_normal((128, 128)))[0][:r].astype(np.float16).view(np.uint16) for r in ranks]
+        flat = np.full((len(ranks), 128 + 16, 128), 0x7e00, dtype=np.uint16)
+        for u, P in enumerate(Ps):
+            flat[u, :P.shape[0]] = P
+        S = kvc.Side(side, ranks, [b] * len(ranks), np.full(len(ranks), step, np.float32), flat.reshape(-1),
+                     np.arange(len(ranks), dtype=np.int64) * 144 * 128, n)
+        kvc.kvc_encode(S, torch.as_tensor(x[side].view(np.int16), device="cuda").view(torch.float16), 0, n)
+        torch.cuda.synchronize()
+        for u, r in enumerate(ranks):
+            codes = onat.encode_codes(Ps[u], float(step), b, x[side, u].view(np.uint16))
+            assert np.array_equal(S.unit_codes(u, n).cpu().numpy(), onat.pack(codes, r, b, side)), (side, r)
