@@ -1128,18 +1128,26 @@ extern template __global__ void decode_partial_kernel<8>(DevSide, DevSide, int, 
 // merged its chunks serially (a wavefront's chunks one batch after another) the combine took more than the
 // partials of a short context: 14.5 us after partials of 6.2 us (8 units x 4k, G = 4), now 5.5; 64 units x 32k
 // 11.7 and 5.4, 256 units x 128k 12.2 and 7.4, 640 units, G = 8, 26 and 18.
+//
+// MANY: more blocks than the chip holds at those registers. The rounds then cost more than the latencies, so the
+// basis is read after the merge and fewer chunks are in flight, which leaves room for five or six blocks per
+// CU where two or four were: a call of 2048 units x 300 tokens takes 40.9 us with one head (50.8 without it), 43.6
+// with two (53.3) and 54.9 with eight (56.8).
 constexpr int kCombThreads = 256;
 constexpr int kCombRows = kCombThreads / 32;  // rows of 32 threads
 // Chunks merged at a time (their weights are in LDS).
-__host__ __device__ constexpr int comb_chunks(int gb) { return gb <= 2 ? 512 : 256; }
+__host__ __device__ constexpr int comb_chunks(int gb, bool many) { return many ? 128 : (gb <= 2 ? 512 : 256); }
 constexpr int kCombMaxHeads = 8;              // heads per block at most
 constexpr int kCombBlocksPerCu = 2;           // blocks at which heads start to share one
-template <int GB>
-__global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(GB <= 2 ? 2 : 4)))
+// Wavefronts per SIMD, and so blocks per CU, that the registers are cut for.
+__host__ __device__ constexpr int comb_waves(int gb, bool many) { return many ? (gb <= 2 ? 6 : 5) : (gb <= 2 ? 2 : 4); }
+template <int GB, bool MANY>
+__global__ __launch_bounds__(kCombThreads) __attribute__((amdgpu_waves_per_eu(comb_waves(GB, MANY))))
 void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ part,
                                                                float* __restrict__ out) {
     static_assert(kCombRows % GB == 0, "a head takes whole rows of threads");
-    constexpr int CS = kCombRows / GB, PF = GB <= 2 ? 8 : 4, RP = kD / kCombRows, NW = kCombThreads / 64, NB = comb_chunks(GB), ML = NB / 64;
+    constexpr int CS = kCombRows / GB, PF = MANY ? 2 : (GB <= 2 ? 8 : 4), RP = kD / kCombRows, NW = kCombThreads / 64;
+    constexpr int NB = comb_chunks(GB, MANY), ML = NB / 64;
     __shared__ float wt[GB][NB];                                   // 2^(m_c - M)
     __shared__ float run[3][GB];                                   // M, L, the batch's rescale
     __shared__ __attribute__((aligned(16))) float red[kCombRows][kD];
@@ -1162,12 +1170,15 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
             if (c < nb) pre[k] = *reinterpret_cast<const float4*>(pa + c * cstride);
         }
     };
-    load_acc(0, min(NB, n_chunks), 0);
+    auto load_basis = [&]() {
 #pragma unroll
-    for (int k = 0; k < RP; ++k) {
-        const int i = row + kCombRows * k;
-        pw[k] = i < rv ? P2[i * (kD / 4)] : uint2{0u, 0u};
-    }
+        for (int k = 0; k < RP; ++k) {
+            const int i = row + kCombRows * k;
+            pw[k] = i < rv ? P2[i * (kD / 4)] : uint2{0u, 0u};
+        }
+    };
+    load_acc(0, min(NB, n_chunks), 0);
+    if constexpr (!MANY) load_basis();
     for (int b0 = 0; b0 < n_chunks; b0 += NB) {
         const int nb = min(NB, n_chunks - b0);
         const float* __restrict__ pb = pu + b0 * cstride;
@@ -1227,6 +1238,7 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
         }
     }
     *reinterpret_cast<float4*>(&red[row][4 * q4]) = A;
+    if constexpr (MANY) load_basis();
     __syncthreads();
     const float step = V.delta[u];
     for (int e = tid; e < GB * kD; e += kCombThreads) {
@@ -1417,19 +1429,29 @@ extern "C" size_t kvc_decode_attn_workspace(const kvc_stream_desc* k, const kvc_
 namespace kvc {
 namespace {
 
+template <bool MANY>
+void launch_combine_g(int gb, dim3 grid, hipStream_t st, const DevSide& V, int G, int n_chunks, const float* part, float* out) {
+    const dim3 blk(kCombThreads);
+    switch (gb) {
+        case 1: hipLaunchKernelGGL((combine_kernel<1, MANY>), grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        case 2: hipLaunchKernelGGL((combine_kernel<2, MANY>), grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        case 4: hipLaunchKernelGGL((combine_kernel<4, MANY>), grid, blk, 0, st, V, G, n_chunks, part, out); break;
+        default: hipLaunchKernelGGL((combine_kernel<8, MANY>), grid, blk, 0, st, V, G, n_chunks, part, out); break;
+    }
+}
+
 // Combine launch for U units of n_chunks partials each. Heads share a block, and so its basis reads, once one
 // head per block makes more blocks than are resident (two per CU at the registers of one or two heads):
-// 256 units, G = 4, 12.1 us with a head per block and 7.4 with two.
+// 256 units, G = 4, 12.1 us with a head per block and 7.4 with two. Blocks beyond what is resident even so take
+// the variant for many: calls of 300 tokens at 640 units, G = 1, 29.4 us without it and 26.1 with it, at 512 units
+// (one round either way) 23.9 and 23.2, at 256 units 15.8 and 16.4.
 void launch_combine(int G, int U, const DevSide& V, int n_chunks, const float* part, float* out, hipStream_t st) {
+    const int64_t cus = device_cus();
     int gb = 1;
-    while (gb < G && gb < kCombMaxHeads && (int64_t)U * G > (int64_t)kCombBlocksPerCu * device_cus() * gb) gb *= 2;
-    const dim3 grid(U, G / gb), blk(kCombThreads);
-    switch (gb) {
-        case 1: hipLaunchKernelGGL(combine_kernel<1>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
-        case 2: hipLaunchKernelGGL(combine_kernel<2>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
-        case 4: hipLaunchKernelGGL(combine_kernel<4>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
-        default: hipLaunchKernelGGL(combine_kernel<8>, grid, blk, 0, st, V, G, n_chunks, part, out); break;
-    }
+    while (gb < G && gb < kCombMaxHeads && (int64_t)U * G > kCombBlocksPerCu * cus * gb) gb *= 2;
+    const dim3 grid(U, G / gb);
+    if ((int64_t)U * (G / gb) > comb_waves(gb, false) * cus) launch_combine_g<true>(gb, grid, st, V, G, n_chunks, part, out);
+    else launch_combine_g<false>(gb, grid, st, V, G, n_chunks, part, out);
 }
 
 // The new token of a fused decode step (none for a plain decode call).
