@@ -5,7 +5,8 @@
 //
 //  * covariance_kernel: C = (1/n) X^T X - mu mu^T per head on fp16 matrix cores
 //    (v_mfma_f32_16x16x32_f16, exact fp16 products, fp32 accumulation), one block of eight
-//    wavefronts per 64 x 64 block of the upper triangle, the tokens shared among the wavefronts.
+//    wavefronts per 64 x 64 block of the upper triangle, the tokens shared among the wavefronts;
+//    covariance_head_kernel, one block of four wavefronts per head, for short runs of many heads.
 //  * eigh_kernel: fp32 parallel cyclic Jacobi (the precision the paper states for its
 //    eigendecomposition). One block per head holds A and the accumulated rotations V in LDS
 //    (2 x 128 x 129 floats). A sweep is 127 rounds of the round-robin ordering; each round
@@ -19,10 +20,12 @@
 //    exact DP over measured distortion) for every candidate rank and width.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
 #include "kvc.h"
+#include "kvc_device.h"
 #include "kvc_internal.h"
 
 namespace kvc {
@@ -203,6 +206,90 @@ __global__ __launch_bounds__(kCovThreads) __attribute__((amdgpu_waves_per_eu(2, 
         const int j = e >> 6, i = e & 63;
         out[(J0 + j) * kD + I0 + i] = sums[i * kCovSumPitch + j];
     }
+}
+
+// Short runs of many heads: one block of four wavefronts per head, which walks the tokens in tiles of 128 staged
+// in LDS (35 KB); a wavefront owns a 64 x 64 quadrant of the output. Its operands are 2-byte gathers and a tile
+// costs about 7 us, but four heads share a CU and there is nothing to add up at the end, where the kernel above
+// needs a CU's LDS for a third of a head and sums eight wavefronts: 256 heads x 128 tokens 11.2 us (21.6
+// there), 2048 heads 48 us (139 there).
+constexpr int kHeadTok = 128;           // tokens staged per step
+constexpr int kHeadPitch = kD + 8;      // LDS row pitch of the staged tokens (halves)
+
+__global__ __launch_bounds__(256) void covariance_head_kernel(const uint16_t* __restrict__ x, int64_t head_stride, int n_tok,
+                                                         int centered, float* __restrict__ cov) {
+    __shared__ __attribute__((aligned(16))) _Float16 xs[kHeadTok * kHeadPitch];
+    __shared__ float msum[16][kD];
+    const int h = blockIdx.x, tid = threadIdx.x, wv = tid >> 6, lane = tid & 63, col = lane & 15, kq = lane >> 4;
+    const uint16_t* __restrict__ X = x + (int64_t)h * head_stride;
+    const int I0 = 4 * (wv >> 1), J0 = 4 * (wv & 1);  // the wavefront's 4 x 4 block of 16 x 16 tiles
+    cv_f4 C[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) C[a][b] = cv_f4{0.f, 0.f, 0.f, 0.f};
+    // partial feature sums: thread handles features 8 (tid % 16) .. + 7 of tokens tid / 16 + 16 k
+    float fs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const int fb = tid & 15, tr = tid >> 4;
+    for (int t0 = 0; t0 < n_tok; t0 += kHeadTok) {
+        // stage 128 tokens (zero past n_tok): 16-byte loads, 8 features of one token each
+#pragma unroll
+        for (int k = 0; k < kHeadTok / 16; ++k) {
+            const int t = tr + 16 * k;
+            uint4 w = uint4{0u, 0u, 0u, 0u};
+            if (t0 + t < n_tok) w = reinterpret_cast<const uint4*>(X + (int64_t)(t0 + t) * kD)[fb];
+            *reinterpret_cast<uint4*>(&xs[t * kHeadPitch + 8 * fb]) = w;
+            const cv_h8 v = __builtin_bit_cast(cv_h8, w);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) fs[e] += (float)v[e];
+        }
+        __syncthreads();
+        // four k-steps of 32 tokens; lane (col, kq) takes tokens 8 kq .. 8 kq + 7 of the step for
+        // feature 16 I + col (A operand, rows = features) and 16 J + col (B operand, columns = features)
+#pragma unroll
+        for (int ks = 0; ks < kHeadTok / 32; ++ks) {
+            cv_h8 fa[4], fbv[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int t = 32 * ks + 8 * kq + e;
+                    fa[a][e] = xs[t * kHeadPitch + 16 * (I0 + a) + col];
+                    fbv[a][e] = xs[t * kHeadPitch + 16 * (J0 + a) + col];
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) C[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[a], fbv[b], C[a][b], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+    // feature means
+#pragma unroll
+    for (int e = 0; e < 8; ++e) msum[tr][8 * fb + e] = fs[e];
+    __syncthreads();
+    __shared__ float mu[kD];
+    if (tid < kD) {
+        float m = 0.f;
+        for (int r = 0; r < 16; ++r) m += msum[r][tid];
+        mu[tid] = m / (float)n_tok;
+    }
+    __syncthreads();
+    const float inv_n = 1.f / (float)n_tok;
+    float* __restrict__ out = cov + (int64_t)h * kD * kD;
+    // lane (col, kq) holds rows 16 I + 4 kq + v, column 16 J + col of tile (I, J)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * (I0 + a) + 4 * kq + v, j = 16 * (J0 + b) + col;
+                float c = C[a][b][v] * inv_n;
+                if (centered) c -= mu[i] * mu[j];
+                out[i * kD + j] = c;
+            }
 }
 
 // ---------------------------------------------------------------- eigendecomposition
@@ -489,8 +576,18 @@ extern "C" int kvc_covariance(const uint16_t* x, int64_t x_head_stride, int32_t 
         return set_error(KVC_EINVAL, "kvc_covariance: x must be 16-byte aligned and the head stride a multiple of 8");
     if (x_head_stride < (int64_t)n_tok * kD) return set_error(KVC_EINVAL, "kvc_covariance: head stride < n_tok * d");
     if (centered != 0 && centered != 1) return set_error(KVC_EINVAL, "kvc_covariance: centered must be 0 or 1");
+    // A block per head is faster up to about one tile of 128 tokens per round of the other kernel's blocks, and up to
+    // 800 tokens: 256 heads (three rounds), 512 tokens, 24.4 us against 26.1, 513 tokens 28.8 against 27.5; 128 heads,
+    // 256 tokens, 13.1 against 13.8, 384 tokens 16.8 against 15.0; 1024 heads, 768 tokens, 87 against 103, 1024
+    // tokens 137 against 123. In one round it is no faster at any length.
+    const int64_t blocks = ((int64_t)n_heads + 7) / 8 * 24, cus = device_cus();
+    if (blocks > cus && n_tok <= std::min<int64_t>((blocks / cus + 1) * kHeadTok, 800)) {
+        hipLaunchKernelGGL(covariance_head_kernel, dim3(n_heads), dim3(256), 0, (hipStream_t)stream, x, x_head_stride, n_tok,
+                           centered, cov);
+        return check_launch_calib("kvc_covariance");
+    }
     if (int e = set_big_lds((const void*)covariance_kernel, kCovLds, "kvc_covariance")) return e;
-    hipLaunchKernelGGL(covariance_kernel, dim3((unsigned)(((int64_t)n_heads + 7) / 8 * 24)), dim3(kCovThreads), kCovLds,
+    hipLaunchKernelGGL(covariance_kernel, dim3((unsigned)blocks), dim3(kCovThreads), kCovLds,
                        (hipStream_t)stream, x, x_head_stride, n_heads, n_tok, centered, cov);
     return check_launch_calib("kvc_covariance");
 }

@@ -160,3 +160,22 @@ def test_covariance_chunk_edges(H, n_tok, centered):
             ref, mag = ref - np.outer(X.mean(0), X.mean(0)), mag + np.outer(np.abs(X).mean(0), np.abs(X).mean(0))
         assert np.all(np.abs(got[h] - ref) <= (n_tok + 8) * 2.0 ** -24 * mag), h
         assert np.array_equal(got[h], got[h].T), h
+
+
+@pytest.mark.parametrize("H,n_tok,centered", [(88, 1, False), (81, 256, True), (88, 257, True), (128, 127, True), (200, 384, False),
+                                              (256, 129, True), (256, 512, True), (256, 513, True), (600, 800, True), (600, 801, False)])
+def test_covariance_short_runs_of_many_heads(H, n_tok, centered):
+    # both sides of the lines between a block per head and three; every sixteenth head is checked, the bound as above
+    rng = np.random.default_rng(H * 1000 + n_tok)
+    x = (rng.standard_normal((H, n_tok, 128), dtype=np.float32) + 0.25 * rng.standard_normal((H, 1, 128), dtype=np.float32)).astype(np.float16)
+    cov = torch.full((H, 128, 128), np.nan, dtype=torch.float32, device="cuda")
+    kvc.kvc_covariance(torch.as_tensor(x.view(np.int16), device="cuda").view(torch.float16), n_tok, cov, centered)
+    torch.cuda.synchronize()
+    got = cov.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    for h in sorted(set(range(0, H, 16)) | {H - 1}):
+        X = x[h].astype(np.float64)
+        ref, mag = X.T @ X / n_tok, np.abs(X).T @ np.abs(X) / n_tok
+        if centered:
+            ref, mag = ref - np.outer(X.mean(0), X.mean(0)), mag + np.outer(np.abs(X).mean(0), np.abs(X).mean(0))
+        assert np.all(np.abs(got[h] - ref) <= (n_tok + 8) * 2.0 ** -24 * mag), h
