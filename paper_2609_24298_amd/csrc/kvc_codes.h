@@ -34,9 +34,9 @@ __host__ __device__ constexpr int bt_coord(int p) {
 
 // Stages P^T (rows of P past the rank are zero, so codes past the rank meet zeros): a thread takes four
 // positions and eight features, lanes consecutive positions.
-template <int side, int THREADS>
-__device__ __forceinline__ void stage_basis_t(uint8_t* __restrict__ PT, const uint16_t* __restrict__ P, int r, int tid) {
-    for (int e = tid; e < (kD / 4) * (kD / 8); e += THREADS) {
+template <int side>
+__device__ __forceinline__ void stage_basis_t(uint8_t* __restrict__ PT, const uint16_t* __restrict__ P, int r, int tid, int threads) {
+    for (int e = tid; e < (kD / 4) * (kD / 8); e += threads) {
         const int w = e & (kD / 4 - 1), f0 = 8 * (e / (kD / 4));
         uint32_t x[4][4];
 #pragma unroll

@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * kRecWaves) __attribute__((amdgpu_waves_per_eu(
     uint8_t* PT = kvc_dsm;
     const int u = blockIdx.y, wv = uni((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int r = uni(s.r[u]), b = uni(s.b[u]);
-    stage_basis_t<side, 64 * kRecWaves>(PT, s.basis + s.basis_off[u], r, threadIdx.x);
+    stage_basis_t<side>(PT, s.basis + s.basis_off[u], r, threadIdx.x, 64 * kRecWaves);
     __syncthreads();
     uint8_t* wl = kvc_dsm + kRecShared + wv * kRecWaveLds;
     float* o = out + (int64_t)u * n_tok * kD;

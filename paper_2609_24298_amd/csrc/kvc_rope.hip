@@ -35,8 +35,8 @@ namespace kvc {
 template <int G> struct RopeShape {
     static constexpr int LM = Shape<G>::LM;
     static constexpr int W = 2;   // wavefronts per SIMD the register budget is cut for
-    // Wavefronts per block (they share P_K^T and the query table): two blocks of four per CU, or one of
-    // eight for G = 8, whose query table does not leave room for two.
+    // Wavefronts per block at most (they share P_K^T and the query table): two blocks of four per CU, or one
+    // of eight for G = 8, whose query table leaves room for two blocks only up to four wavefronts (rope_waves).
     static constexpr int kWaves = G == 8 ? 8 : 4;
     static constexpr int kPt = kBtBytes;                             // P_K^T
     static constexpr int kKey = 4 * 64 * 8 * 4;                      // cos, sin of 4 col positions: [rb][2][lane] float4
@@ -318,14 +318,15 @@ __device__ __attribute__((always_inline)) void rope_item(const DevSide& K, const
     write_partial<G>(C, mrun, rv, hv, out, lane);
 }
 
-// Block (chunks blockIdx.x kWaves .., unit, heads blockIdx.z G .. of the unit's Gq): one wavefront per chunk.
+// Block (chunks blockIdx.x nw .., unit, heads blockIdx.z G .. of the unit's Gq): one wavefront per chunk, nw of them.
 template <int G>
 __global__ __launch_bounds__(64 * RopeShape<G>::kWaves) __attribute__((amdgpu_waves_per_eu(RopeShape<G>::W, RopeShape<G>::W)))
 void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, int Gq, const int32_t* __restrict__ seq_len, int max_seq,
                         int chunk, int n_chunks, int k_cap_tiles, int v_cap_tiles, double log2_base, int wave_lds,
                         float* __restrict__ part) {
     using R = RopeShape<G>;
-    constexpr int LM = R::LM, T = 64 * R::kWaves;
+    constexpr int LM = R::LM;
+    const int nw = G == 8 ? uni((int)(blockDim.x >> 6)) : R::kWaves, T = 64 * nw;
     const int u = blockIdx.y, tid = threadIdx.x, wv = uni(tid >> 6), lane = tid & 63, col = lane & 15, grp = lane >> 4;
     const int rk = uni(K.r[u]), bk = uni(K.b[u]);
     uint8_t* sm = kvc_dsm;
@@ -334,7 +335,7 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, in
     double* om = reinterpret_cast<double*>(sm + R::kPt + R::kKey + R::kQry);
     float* qsc = reinterpret_cast<float*>(sm + R::kPt + R::kKey + R::kQry + 64 * 8);
     if (tid < 64) om[tid] = exp2(-(double)tid / 64.0 * log2_base) * 0.15915494309189535;  // turns per position of pair tid
-    stage_basis_t<KVC_SIDE_K, T>(sm, K.basis + K.basis_off[u], rk, tid);
+    stage_basis_t<KVC_SIDE_K>(sm, K.basis + K.basis_off[u], rk, tid, T);
     __syncthreads();
     // cos, sin of n positions of pair j (turns reduced in fp64)
     auto turn = [&](int n, int j, float& c, float& sn) {
@@ -349,7 +350,7 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, in
         dst[0] = c;
         dst[1] = sn;
     }
-    for (int lm = wv; lm < LM; lm += R::kWaves) {  // row 4 h + st of the query operand: lane (col, grp), head 4 lm + col / 4
+    for (int lm = wv; lm < LM; lm += nw) {  // row 4 h + st of the query operand: lane (col, grp), head 4 lm + col / 4
         const int hd = 4 * lm + (col >> 2), st = col & 3;
         float a[4][4], b[4][4], m = 0.f;
 #pragma unroll
@@ -385,7 +386,7 @@ void decode_rope_kernel(DevSide K, DevSide V, const uint16_t* __restrict__ q, in
         if (hd < G && st == 0 && grp == 0) qsc[hd] = ldexpf(K.delta[u] * 1.4426950408889634f * 0.08838834764831845f, -ex);
     }
     __syncthreads();
-    const int c = blockIdx.x * R::kWaves + wv;
+    const int c = blockIdx.x * nw + wv;
     if (c >= n_chunks) return;  // no block-wide barrier follows
     int Tn = uni(seq_len[u]);
     Tn = Tn < 0 ? 0 : (Tn > max_seq ? max_seq : Tn);
@@ -412,6 +413,22 @@ extern template __global__ void decode_rope_kernel<8>(DevSide, DevSide, const ui
 
 namespace {
 
+constexpr int kLdsPerCu = 160 * 1024;
+
+// Wavefronts per block for n_chunks chunks per unit. With G = 8 and few chunks the wavefronts of a block of eight
+// past the last chunk would idle while its LDS keeps a second block off the CU: up to four chunks take blocks
+// of four wavefronts (three where the widest staged K-step needs it), two per CU. 2048 units x 300 tokens,
+// 2 bpd: 398 -> 238 us, sixteen heads 776 -> 452 (780 in one item of sixteen heads); 256 units x 8192 tokens,
+// 3 bpd, sixteen heads (four chunks): 648 -> 428 (618). Five chunks and more fill most of a block of eight.
+template <int G>
+int rope_waves(int n_chunks, int wave_lds) {
+    using R = RopeShape<G>;
+    if (G != 8 || n_chunks > 4) return R::kWaves;
+    int nw = 4;
+    while (nw > 1 && 2 * (R::kShared + nw * wave_lds) > kLdsPerCu) --nw;
+    return nw;
+}
+
 // Gq query heads per unit, G of them per item.
 template <int G>
 int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint16_t* q, int Gq, const int32_t* seq_len, int32_t max_seq_len,
@@ -420,7 +437,7 @@ int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
     const int U = k->n_units, tpu = (max_seq_len + kTile - 1) / kTile;
     const int kct = (k->capacity + kTile - 1) / kTile, vct = (v->capacity + kTile - 1) / kTile;
     const int wave_lds = R::kWave + (stage_bytes + 15) / 16 * 16;
-    const size_t smem = (size_t)R::kShared + (size_t)R::kWaves * wave_lds;
+    const size_t smem = (size_t)R::kShared + (size_t)R::kWaves * wave_lds;  // of the largest block
     if (smem > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void*)decode_rope_kernel<G>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return set_error(KVC_EDEVICE, "hipFuncSetAttribute: %s", hipGetErrorString(e));
@@ -438,8 +455,9 @@ int launch_rope_g(const kvc_stream_desc* k, const kvc_stream_desc* v, const uint
         if (best < 0.0 || cost < best) { best = cost; best_n = n; best_c = c; }
     }
     *n_chunks = best_n;
-    hipLaunchKernelGGL(decode_rope_kernel<G>, dim3((best_n + R::kWaves - 1) / R::kWaves, U, Gq / G), dim3(64 * R::kWaves), smem, st, dev_side(k),
-                       dev_side(v), q, Gq, seq_len, max_seq_len, best_c * kTile, best_n, kct, vct, log2_base, wave_lds, part);
+    const int nw = rope_waves<G>(best_n, wave_lds);
+    hipLaunchKernelGGL(decode_rope_kernel<G>, dim3((best_n + nw - 1) / nw, U, Gq / G), dim3(64 * nw),
+                       (size_t)R::kShared + (size_t)nw * wave_lds, st, dev_side(k), dev_side(v), q, Gq, seq_len, max_seq_len, best_c * kTile, best_n, kct, vct, log2_base, wave_lds, part);
     return check_launch("kvc_decode_attn_rope");
 }
 
