@@ -42,7 +42,7 @@ __device__ __forceinline__ void stage_basis_t(uint8_t* __restrict__ PT, const ui
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = bt_coord<side>(4 * w + j);
-            const uint4 v = i < r ? *reinterpret_cast<const uint4*>(P + (int64_t)i * kD + f0) : uint4{0u, 0u, 0u, 0u};
+            const uint4 v = i < r ? load_basis8(P + (int64_t)i * kD + f0) : uint4{0u, 0u, 0u, 0u};
             x[j][0] = v.x; x[j][1] = v.y; x[j][2] = v.z; x[j][3] = v.w;
         }
 #pragma unroll

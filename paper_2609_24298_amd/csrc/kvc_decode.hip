@@ -1158,7 +1158,7 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
     const float* __restrict__ pu = part + ((int64_t)u * n_chunks * G + h0) * kPartStride;
     const int64_t cstride = (int64_t)G * kPartStride;
     const int rv = V.r[u];
-    const uint2* __restrict__ P2 = reinterpret_cast<const uint2*>(V.basis + V.basis_off[u]) + q4;
+    const uint16_t* __restrict__ P4 = V.basis + V.basis_off[u] + 4 * q4;
     uint2 pw[RP];
     float4 A = float4{0.f, 0.f, 0.f, 0.f}, pre[PF];
     // coordinates 4 q4 .. of chunks c0 + cr + k CS of the batch of nb chunks at b0
@@ -1174,7 +1174,7 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
 #pragma unroll
         for (int k = 0; k < RP; ++k) {
             const int i = row + kCombRows * k;
-            pw[k] = i < rv ? P2[i * (kD / 4)] : uint2{0u, 0u};
+            pw[k] = i < rv ? load_basis4(P4 + i * kD) : uint2{0u, 0u};
         }
     };
     load_acc(0, min(NB, n_chunks), 0);

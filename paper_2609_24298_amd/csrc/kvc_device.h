@@ -134,6 +134,19 @@ __host__ __device__ constexpr int plane_off(int b, int k) { return b == 8 ? 0 : 
         default: { constexpr int B_ = 8; CALL; } break;      \
     }
 
+// Consecutive basis entries by one wide load: a unit's basis may start at any element (basis_off is not
+// restricted), and global memory takes wide loads at any address.
+struct __attribute__((packed, aligned(2))) Basis4 { uint32_t x, y; };
+struct __attribute__((packed, aligned(2))) Basis8 { uint32_t x, y, z, w; };
+__device__ __forceinline__ uint2 load_basis4(const uint16_t* p) {
+    const Basis4 v = *reinterpret_cast<const Basis4*>(p);
+    return uint2{v.x, v.y};
+}
+__device__ __forceinline__ uint4 load_basis8(const uint16_t* p) {
+    const Basis8 v = *reinterpret_cast<const Basis8*>(p);
+    return uint4{v.x, v.y, v.z, v.w};
+}
+
 // fp16 bits -> fp32 (exact).
 __device__ __forceinline__ float h2f(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 

@@ -109,3 +109,26 @@ def test_combine_many_blocks():
 def test_combine_many_blocks_long():
     # 513 units of 33100 tokens: a second pass for one head, a third for two
     _check(CAP, 171, (1, 2), {1: 17, 2: 17})
+
+
+def test_combine_basis_at_any_element():
+    # the value bases start at odd elements of the arena
+    rng = np.random.default_rng(23)
+    T = 300
+    xs = [(rng.standard_normal((len(ROWS), T, 128)) * 0.6).astype(np.float16) for _ in range(2)]
+    K = _side(kvc.SIDE_K, xs[0], rng, 1)[0]
+    V, Pv, dv, bv, _ = _side(kvc.SIDE_V, xs[1], rng, 1)
+    offs = np.array([1, 3, 5], dtype=np.int64) + np.concatenate([[0], np.cumsum([p.size for p in Pv])[:-1]])
+    flat = np.full(int(offs[-1]) + Pv[-1].size, 0x7e00, dtype=np.uint16)
+    for o, p in zip(offs, Pv):
+        flat[o:o + p.size] = p.reshape(-1)
+    W = kvc.Side(kvc.SIDE_V, V.r_h, V.b_h, np.array(dv, np.float32), flat, offs, T, codes=V.codes)
+    q = torch.as_tensor((rng.standard_normal((3, 4, 128)) * 3.0).astype(np.float16).view(np.int16), device="cuda").view(torch.float16)
+    seq = torch.full((3,), T, dtype=torch.int32, device="cuda")
+    ws = torch.empty(kvc.kvc_decode_attn_workspace(K, V, 4, T), dtype=torch.uint8, device="cuda")
+    outs = [torch.full((3, 4, 128), np.nan, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for side, out in zip((V, W), outs):
+        kvc.kvc_decode_attn(K, side, q, 4, seq, T, out, ws)
+    torch.cuda.synchronize()
+    a, b = (o.cpu().numpy() for o in outs)
+    assert np.isfinite(a).all() and np.array_equal(a, b)

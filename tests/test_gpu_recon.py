@@ -41,3 +41,28 @@ def test_reconstruct_ranges(side, t0, n, shift):
         codes = onat.encode_codes(Ps[u], float(ds[u]), b, x[u, t0:t0 + n].view(np.uint16))
         ref = oatt.reconstruct(codes, Ps[u], float(ds[u]), b)
         assert np.max(np.abs(got[u] - ref)) <= 2.0 ** -16 * np.max(np.abs(ref)), (r, b)
+
+
+@pytest.mark.parametrize("side", [kvc.SIDE_K, kvc.SIDE_V])
+def test_reconstruct_basis_at_any_element(side):
+    # bases that start at odd elements of the arena reconstruct what aligned ones do, bit for bit
+    rng = np.random.default_rng(5)
+    ranks, b, n = (2, 30, 64, 66, 128), 3, 70
+    Ps = [np.linalg.qr(rng.standard_normal((128, 128)))[0][:r].astype(np.float16).view(np.uint16).reshape(-1) for r in ranks]
+    x = torch.as_tensor(rng.standard_normal((len(ranks), n, 128)).astype(np.float16).view(np.int16), device="cuda").view(torch.float16)
+    got, codes = [], None
+    for gap in (0, 1, 3):
+        offs = np.array([gap * (u + 1) + sum(p.size for p in Ps[:u]) for u in range(len(ranks))], dtype=np.int64)
+        flat = np.full(int(offs[-1]) + Ps[-1].size, 0x7e00, dtype=np.uint16)
+        for o, p in zip(offs, Ps):
+            flat[o:o + p.size] = p
+        S = kvc.Side(side, ranks, [b] * len(ranks), np.full(len(ranks), 0.4, np.float32), flat, offs, n, codes=codes)
+        if codes is None:
+            kvc.kvc_encode(S, x, 0, n)
+            codes = S.codes
+        out = torch.full((len(ranks), n, 128), np.nan, dtype=torch.float32, device="cuda")
+        kvc.kvc_reconstruct(S, 0, n, out)
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+    assert np.isfinite(got[0]).all()
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
