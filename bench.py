@@ -51,10 +51,13 @@ def decode_alg_bytes(cache, n_tok: int) -> int:
 
 
 def kernel_source_hash() -> str:
+    """Hash of every device source and header of the library."""
     h = hashlib.sha256()
-    for f in ("kvc_kernels.hip", "kvc_decode.hip", "kvc_decode_g4.hip", "kvc_decode_g8.hip", "kvc_device.h",
-              "kvc_append.h"):
-        with open(os.path.join(ROOT, "paper_2609_24298_amd", "csrc", f), "rb") as fh:
+    csrc = os.path.join(ROOT, "paper_2609_24298_amd", "csrc")
+    files = [os.path.join(csrc, f) for f in sorted(os.listdir(csrc)) if f.endswith((".hip", ".h"))]
+    for f in files:
+        h.update(os.path.basename(f).encode())
+        with open(f, "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 

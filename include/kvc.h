@@ -321,8 +321,8 @@ int kvc_decode_attn_noalloc(const kvc_stream_desc* k, const kvc_stream_desc* v, 
 /*
  * kvc_encode_kv - kvc_encode of the keys and the values of the same tokens in one call.
  * Paper: table step 7-8 (a decode step caches the new token's key and value). For
- * n_tok <= 4 (appending a decode step's tokens) both sides run in one launch; longer
- * runs take the bulk encoder, one launch per side. Codes are those kvc_encode writes.
+ * n_tok <= 4 (appending a decode step's tokens) the append kernel takes both sides, for
+ * longer runs the bulk encoder, in one launch either way. Codes are those kvc_encode writes.
  *  k, v          descriptors of the K (side 0) and V (side 1) streams, same n_units.
  *  xk, xv        device fp16 tokens of each side, laid out as kvc_encode's x.
  * Same requirements and errors as kvc_encode for each side, plus KVC_EINVAL for

@@ -305,10 +305,9 @@ __device__ __forceinline__ void k_fetch(uint32_t* w, const __amdgpu_buffer_rsrc_
 // Prefetch of a unit's first tile (both K-steps, for the widths whose two K-steps fit the prefetch
 // registers; wider codes are loaded when their tile is processed).
 template <int B, int KM>
-__device__ __forceinline__ void k_prefetch(uint32_t (&kb)[kKBufWords], const __amdgpu_buffer_rsrc_t rs, int rk, int nk,
-                                           int ks_t, const uint32_t (&LK)[2], int lane) {
+__device__ __forceinline__ void k_prefetch(uint32_t (&kb)[kKBufWords], const __amdgpu_buffer_rsrc_t rs, int rk,
+                                           const uint32_t (&LK)[2]) {
     constexpr int W0 = k_step_words(B);
-    (void)nk;
     if constexpr (k_prefetch_on(B, KM)) {
         k_fetch<B>(kb, rs, rk, LK[0]);
         if constexpr (k_second_load(B)) k_fetch<B>(kb + W0, rs, rk, LK[1]);
@@ -547,7 +546,7 @@ __device__ __forceinline__ void v_tile(uint32_t* vb, const __amdgpu_buffer_rsrc_
 // limbs with q~ ~ sigma (L0 + L1/254 + L2/254^2). The limbs are written as the logit MFMA's A
 // operand of every lane: qa[u][ks][lm][lane] = 16 bytes, lane (grp, row = 4 (h % 4) + limb), lm = h / 4,
 // operand byte m <-> coordinate 16 (4 ks + grp) + pos_b(m) (zero outside the rank, for limb 3 and for
-// heads >= G). qk[u][h] = (sigma, sigma / 254, sigma / 254^2, bias) with
+// heads >= G). qk[u][h] = (sigma, 0, sigma / 254^2, bias) with
 // bias = -2^(b-1) sum_limb k_limb sum_i L_limb,i (0 for b = 8, whose codes are centred on load).
 typedef _Float16 qp_h8 __attribute__((ext_vector_type(8)));
 typedef float qp_f4 __attribute__((ext_vector_type(4)));
@@ -672,7 +671,7 @@ __device__ __forceinline__ void qprep_unit(const DevSide& K, const uint16_t* __r
         if (wv == 0 && kq == 0 && g < G) {
             const float k0 = sigma, k1 = sigma * (1.f / 254.f), k2 = sigma * (1.f / 64516.f);
             const float bias = -(float)hk * ((float)lsum[0] * k0 + (float)lsum[1] * k1 + (float)lsum[2] * k2);
-            qk[(int64_t)u * G + g] = float4{k0, k1, k2, bias};
+            qk[(int64_t)u * G + g] = float4{k0, 0.f, k2, bias};
         }
         if constexpr (NW > 1) __syncthreads();  // red_m, red_l are rewritten by the next head group
     }
@@ -938,13 +937,13 @@ __device__ __attribute__((always_inline)) void run_item(const DevSide& K, const 
         // issued in the loop's own order (K-steps, then value N-tiles, per set), so that the waits at
         // the loop head count the same younger loads on entry as on the back edge
         const auto krs = k_rs(tile0), vrs = v_rs(tile0);
-        KVC_SW_K((k_prefetch<B_, KM>(kbA, krs, rk, nk, ks_t, LK, lane)));
+        KVC_SW_K((k_prefetch<B_, KM>(kbA, krs, rk, LK)));
         __builtin_amdgcn_sched_barrier(0);
         KVC_SW_V((v_prefetch<B_, NVc>(vbA, vrs, rv, LV, VA)));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (kDepth == 2) {
             const auto krs1 = k_rs(tile0 + 1), vrs1 = v_rs(tile0 + 1);
-            KVC_SW_K((k_prefetch<B_, KM>(kbB, krs1, rk, nk, ks_t, LK, lane)));
+            KVC_SW_K((k_prefetch<B_, KM>(kbB, krs1, rk, LK)));
             __builtin_amdgcn_sched_barrier(0);
             KVC_SW_V((v_prefetch<B_, NVc>(vbB, vrs1, rv, LV, VA)));
             __builtin_amdgcn_sched_barrier(0);
@@ -1053,7 +1052,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(Shape<G>::W,
     constexpr int LM = Shape<G>::LM;
 
     const int u = blockIdx.y, c = blockIdx.x, lane = threadIdx.x;
-    const int col = lane & 15, grp = lane >> 4;
     int T = seq_len[u];
     T = T < 0 ? 0 : (T > max_seq ? max_seq : T);
     const int start = c * chunk;

@@ -33,22 +33,6 @@ __host__ __device__ constexpr int kidx_b(int b, int j) {
     return b == 8 ? j : (b == 4 ? 8 * (j >> 3) + 4 * (j & 1) + ((j & 7) >> 1) : 4 * (j & 3) + (j >> 2));
 }
 
-// Slot of (token t in tile, coordinate i) on the K side: token-major inside groups of 16
-// coordinates (a token's 16 codes of a group are 16 consecutive slots), the r % 16 tail group
-// token-major after them; slot phi of a plane of width p holds bits [p phi, p phi + p).
-__device__ __forceinline__ int slot_k(int t, int i, int r) {
-    const int g16 = r >> 4;
-    if (i < 16 * g16) return ((i >> 4) << 10) + (t << 4) + (i & 15);
-    return (g16 << 10) + t * (r & 15) + (i - 16 * g16);
-}
-// Inverse of slot_k: token and coordinate of slot phi.
-__device__ __forceinline__ void unslot_k(int phi, int r, int& t, int& i) {
-    const int g16 = r >> 4;
-    if (phi < (g16 << 10)) { t = (phi >> 4) & 63; i = ((phi >> 10) << 4) + (phi & 15); return; }
-    const int rho = r & 15, q = phi - (g16 << 10);
-    t = q / rho;
-    i = 16 * g16 + (q - t * rho);
-}
 // V fields: the 16 codes of coordinate 16 n + c (N-tile n, column c) for the tokens of quarter q of
 // the tile, token t at position pos_b(t % 16), p bits each: 2p bytes. In a plane of width p the
 // N-tiles form groups of g = 8 / p (g = 1 for p = 8), group Q at byte 1024 Q of the plane, and a
@@ -69,43 +53,6 @@ __host__ __device__ inline int v_field_off(int p, int r, int n, int c, int q) {
 // Bit of the code of (token t in tile, coordinate i) in the V plane of width p.
 __host__ __device__ inline int v_plane_bit(int t, int i, int r, int b, int p) {
     return 8 * v_field_off(p, r, i >> 4, i & 15, t >> 4) + p * pos_b(b, t & 15);
-}
-
-// Code stored in K slot phi of the tile starting at `tile`: the p bits of each plane
-// (widest first) sit at bits [p phi, p phi + p) of the plane.
-__device__ __forceinline__ uint32_t load_code(const uint8_t* __restrict__ tile, int r, int b, int phi) {
-    if (b == 8) return tile[phi];
-    uint32_t c = 0;
-    int rem = b;
-    int off = 0;
-#pragma unroll
-    for (int p = 4; p >= 1; p >>= 1) {
-        if (b & p) {
-            const int bit = p * phi;
-            rem -= p;
-            c |= ((uint32_t)(tile[off + (bit >> 3)] >> (bit & 7)) & ((1u << p) - 1u)) << rem;
-            off += 8 * r * p;
-        }
-    }
-    return c;
-}
-
-// Code of (token t in tile, coordinate i) on the V side.
-__device__ __forceinline__ uint32_t load_code_v(const uint8_t* __restrict__ tile, int r, int b, int t, int i) {
-    if (b == 8) return tile[v_plane_bit(t, i, r, 8, 8) >> 3];
-    uint32_t c = 0;
-    int rem = b;
-    int off = 0;
-#pragma unroll
-    for (int p = 4; p >= 1; p >>= 1) {
-        if (b & p) {
-            const int bit = v_plane_bit(t, i, r, b, p);
-            rem -= p;
-            c |= ((uint32_t)(tile[off + (bit >> 3)] >> (bit & 7)) & ((1u << p) - 1u)) << rem;
-            off += 8 * r * p;
-        }
-    }
-    return c;
 }
 
 // Planes of a b-bit code, widest first (b = 8: one plane): width of plane k, its bit

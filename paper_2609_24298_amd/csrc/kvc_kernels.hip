@@ -406,7 +406,7 @@ __device__ __forceinline__ void encode_tiles(const uint16_t* __restrict__ Pl, co
                         if (fabsf(tp - __builtin_rintf(tp)) >= thr[nt]) ambm |= 1u << (4 * nt + i);
                     }
                 // a token long enough makes thr negative and flags even the coordinates past the rank
-                ambm &= encode_rank_mask(side, r - 16 * mc, col, grp);
+                if (mc == g16) ambm &= encode_rank_mask(side, r - 16 * mc, col, grp);
                 uint64_t pend = __ballot(ambm != 0);
                 while (pend) {
                     const int L = __builtin_ctzll(pend);

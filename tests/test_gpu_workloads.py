@@ -190,9 +190,8 @@ def test_decode_every_group_size(G):
 
 @pytest.mark.parametrize("G", [1, 4, 8, 16])
 def test_decode_many_chunks_every_group_size(G):
-    # two units over 65 tiles: the context splits into more than 32 chunks, so the combine runs with
-    # its widest block for the group size (8 wavefronts for G <= 4, 4 for G = 8, 2 for G = 16) and the
-    # query projection on eight wavefronts per unit
+    # two units over 65 tiles: the context splits into more chunks than a wavefront has lanes, so the combine
+    # (one head per block) merges them in two passes, and the query projection runs on eight wavefronts per unit
     w = synth.Workload(f"chunks_g{G}", layers=1, kv_heads=1, group=G, batch=2, tokens=4100, bpd=2.0)
     log(f"[chunks G={G}] build")
     cache, xk, xv = _build(w, w.tokens, w.tokens)
@@ -249,7 +248,8 @@ def test_70b_shape_sampled_parity():
 
 @pytest.mark.parametrize("G,T,bpd", [(16, 32768, 2.0), (1, 131072, 1.0)])
 def test_peaky_attention_long_chunks_other_group_sizes(G, T, bpd):
-    # 256 units, so the context splits into few long chunks, with the general-width partials kernel
+    # 256 units, so the context splits into few long chunks: sixteen heads as two compiled items of eight, one
+    # head on the general-width partials path
     w = synth.Workload(f"peaky_g{G}_t{T}", 32, 8, G, 1, T, bpd)
     _sampled_full(w, T, [1, 200], peaky=True)
 
