@@ -1146,6 +1146,10 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
     static_assert(kCombRows % GB == 0, "a head takes whole rows of threads");
     constexpr int CS = kCombRows / GB, PF = MANY ? 2 : (GB <= 2 ? 8 : 4), RP = kD / kCombRows, NW = kCombThreads / 64;
     constexpr int NB = comb_chunks(GB, MANY), ML = NB / 64;
+    // With four or eight heads a thread takes every chunk or every other one: the sum of a pass is formed apart, so
+    // that the roundings of the whole sum grow with the passes (in one chain the outputs of 640 units x 64k, G = 8, 16
+    // chunks, were 2.4e-6 off fp64; with two chains per unit, before, 2.2e-6).
+    constexpr bool kSub = !MANY && GB >= 4;
     __shared__ float wt[GB][NB];                                   // 2^(m_c - M)
     __shared__ float run[3][GB];                                   // M, L, the batch's rescale
     __shared__ __attribute__((aligned(16))) float red[kCombRows][kD];
@@ -1223,16 +1227,19 @@ void combine_kernel(DevSide V, int G, int n_chunks, const float* __restrict__ pa
         }
         for (int c0 = 0; c0 < nb; c0 += PF * CS) {
             if (c0 > 0) load_acc(b0, nb, c0);
+            float4 p = kSub ? float4{0.f, 0.f, 0.f, 0.f} : A;
 #pragma unroll
             for (int k = 0; k < PF; ++k) {
                 const int c = c0 + cr + k * CS;
                 const float w = c < nb ? wt[hr][c] : 0.f;
                 const bool on = w != 0.f;  // an empty chunk's accumulator is not written
-                A.x = fmaf(on ? pre[k].x : 0.f, w, A.x);
-                A.y = fmaf(on ? pre[k].y : 0.f, w, A.y);
-                A.z = fmaf(on ? pre[k].z : 0.f, w, A.z);
-                A.w = fmaf(on ? pre[k].w : 0.f, w, A.w);
+                p.x = fmaf(on ? pre[k].x : 0.f, w, p.x);
+                p.y = fmaf(on ? pre[k].y : 0.f, w, p.y);
+                p.z = fmaf(on ? pre[k].z : 0.f, w, p.z);
+                p.w = fmaf(on ? pre[k].w : 0.f, w, p.w);
             }
+            if constexpr (kSub) A = float4{A.x + p.x, A.y + p.y, A.z + p.z, A.w + p.w};
+            else A = p;
         }
     }
     *reinterpret_cast<float4*>(&red[row][4 * q4]) = A;
