@@ -34,6 +34,11 @@
 // accumulators hold every limb of one (head, coordinate) in one lane, so a raise
 // of the max rescales them exactly in place. A second kernel merges the chunks
 // and applies step_V and the V basis.
+//
+// What bounds the partials: at 2 bpd (2048 units x 32k) HBM reads, near their ceiling, and each
+// wavefront's serial chain per tile (203 VALU instructions, the VALU busy 48 % of the time, wavefronts
+// ready but not issued 60 %); at 0.5 bpd (256 units x 128k, 152 VALU instructions per tile) the
+// issue of VALU instructions, which keeps it busy 76 %.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
