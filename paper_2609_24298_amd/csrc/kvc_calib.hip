@@ -20,7 +20,6 @@
 //    exact DP over measured distortion) for every candidate rank and width.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdint>
 
@@ -580,8 +579,13 @@ extern "C" int kvc_covariance(const uint16_t* x, int64_t x_head_stride, int32_t 
     // 800 tokens: 256 heads (three rounds), 512 tokens, 24.4 us against 26.1, 513 tokens 28.8 against 27.5; 128 heads,
     // 256 tokens, 13.1 against 13.8, 384 tokens 16.8 against 15.0; 1024 heads, 768 tokens, 87 against 103, 1024
     // tokens 137 against 123. In one round it is no faster at any length.
-    const int64_t blocks = ((int64_t)n_heads + 7) / 8 * 24, cus = device_cus();
-    if (blocks > cus && n_tok <= std::min<int64_t>((blocks / cus + 1) * kHeadTok, 800)) {
+    const int64_t blocks = ((int64_t)n_heads + 7) / 8 * 24;
+    bool per_head = false;
+    if (n_tok <= 800 && blocks > 128) {  // half of the chip: not worth asking for the CUs (0.3 us of a call of 8.3)
+        const int64_t cus = device_cus();
+        per_head = blocks > cus && n_tok <= (blocks / cus + 1) * kHeadTok;
+    }
+    if (per_head) {
         hipLaunchKernelGGL(covariance_head_kernel, dim3(n_heads), dim3(256), 0, (hipStream_t)stream, x, x_head_stride, n_tok,
                            centered, cov);
         return check_launch_calib("kvc_covariance");
